@@ -236,16 +236,15 @@ labs_status labs_walk_step1_bloom(const labs_step1_cfg* cfg, const labs_bloom* b
                                   labs_step1_out* out, void* ws, size_t ws_bytes, void* stream);
 
 /* ----------------------------------------------------------------------------
- * Autotuner of the walker's tiles.  A shape class is (NW, R): NW = ceil(k/32)
- * words of even lags and R = ceil((k+1-p)/64) free positions per lane.  Its tile
- * is RB, the slots a lane scans per pass (R, or ceil(R/2) to free registers for
- * occupancy), and the resident waves per SIMD requested by persistent launches
- * (1, 2, 3, 4 or 8).  Untuned, RB is R unless that kernel keeps at most three
- * waves per SIMD resident and the ceil(R/2) kernel keeps more, and persistent
- * launches request 2 waves per SIMD.  labs_autotune_step1 times every candidate tile on the largest
+ * Autotuner of the walker's persistent launches.  A shape class is (NW, R): NW =
+ * ceil(k/32) words of even lags and R = ceil((k+1-p)/64) groups of free positions (at
+ * least ceil(NW/2) - 1).  What is tuned is the resident waves per SIMD that persistent
+ * launches request (1, 2, 3, 4 or 8; untuned 5); a table's RB (R or ceil(R/2)) is kept
+ * and reported, and every kernel scans all positions at once.  labs_autotune_step1
+ * times every candidate on the largest
  * length of each class among Ls (host array of n_L odd lengths) with `walkers`
  * walkers x `steps` steps, and keeps the fastest in a process-wide table used by
- * every later walk.  It allocates and frees its own scratch and synchronises
+ * every later batched walk.  It allocates and frees its own scratch and synchronises
  * `stream`.  The table can be written to / read from a JSON file; labs_autotune_get
  * reports the tile used for (L, p) (host outputs).
  */

@@ -5,6 +5,7 @@
 #include "walk_impl.h"
 
 #include <algorithm>
+#include <array>
 #include <climits>
 #include <cstdio>
 #include <cstring>
@@ -19,10 +20,14 @@ namespace labsdev {
 namespace {
 
 struct Tile {
-    int RB;        // slots per pass
+    int RB;        // slots per pass as the table files name it; every kernel scans all of them
     int waves;     // resident waves per SIMD requested for persistent launches
     double ms;     // measured time of the winning trial (0 when untuned)
 };
+
+// Waves per SIMD a persistent launch asks for untuned: as many as the widest kernels
+// keep resident (workgroups beyond the residency find the queue empty and leave).
+constexpr int kDefaultWaves = 5;
 
 std::mutex g_mu;
 std::map<std::pair<int, int>, Tile> g_tiles;   // (NW, R) -> tile
@@ -31,45 +36,23 @@ struct Shape {
     int NW, R;
 };
 
+// A class's slot groups R lie in {ceil(NW/2) - 1, ceil(NW/2), ceil(NW/2) + 1}, at least
+// 1; a long prefix counts as the smallest.
+int min_groups(int NW) { return std::max((NW + 1) / 2 - 1, 1); }
+
 Shape shape_of(int L, int p) {
     const int k = (L - 1) / 2;
     Shape s;
     s.NW = (k + 31) / 32;
-    s.R = (k + 1 - p + 63) / 64;
-    WalkKernels wk;
-    if (walk_kernels_lookup(s.NW, s.R, s.R, &wk)) s.R = wk.R;   // instantiated R
+    s.R = std::max((k + 1 - p + 63) / 64, min_groups(s.NW));
     return s;
-}
-
-// The untuned slot tile of a shape: all R slot groups in one pass, unless that
-// kernel keeps at most three waves per SIMD resident and the half tile keeps more
-// (the half tile ballots the planes twice per step, which the extra wave more than
-// pays for there: L = 409, p = 12, three against four waves: 1.30 -> 1.34e11
-// flip-evals/s; where both keep three, at L = 451, 501 and 527, or the full tile
-// keeps four, at L = 387, the full tile is faster).
-std::map<std::pair<int, int>, int> g_default_rb;   // guarded by g_mu
-
-int default_rb(const Shape& s) {
-    const int half = (s.R + 1) / 2;
-    if (half == s.R) return s.R;
-    WalkKernels full, hk;
-    if (!walk_kernels_lookup(s.NW, s.R, s.R, &full) || !walk_kernels_lookup(s.NW, s.R, half, &hk) ||
-        full.RB != s.R || hk.RB != half)
-        return s.R;
-    int bf = 0, bh = 0;   // resident one-wave workgroups per CU (four SIMDs)
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, (const void*)full.plain, 64, 0) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&bh, (const void*)hk.plain, 64, 0) != hipSuccess)
-        return s.R;
-    return (bf <= 12 && bh > bf) ? half : s.R;
 }
 
 Tile tile_for(const Shape& s) {
     std::lock_guard<std::mutex> g(g_mu);
     auto it = g_tiles.find({s.NW, s.R});
     if (it != g_tiles.end()) return it->second;
-    auto d = g_default_rb.find({s.NW, s.R});
-    if (d == g_default_rb.end()) d = g_default_rb.emplace(std::make_pair(s.NW, s.R), default_rb(s)).first;
-    return Tile{d->second, 2, 0.0};
+    return Tile{s.R, kDefaultWaves, 0.0};
 }
 
 int cu_count() {
@@ -175,6 +158,8 @@ struct ClassRun {
     unsigned grid;
 };
 
+typedef std::array<int, 4> ClassKey;   // KH, NT, NQ, waves
+
 struct Plan {
     WalkArgs* args_h = nullptr;   // pinned
     int2* items_h = nullptr;      // pinned
@@ -228,7 +213,8 @@ labs_status build_plan(const labs_step1_cfg* c, int n, const labs_step1_out* out
     LABS_HIP(hipHostMalloc((void**)&P->args_h, sizeof(WalkArgs) * n, hipHostMallocDefault));
     LABS_HIP(hipHostMalloc((void**)&P->items_h, sizeof(int2) * (bl.n_items ? bl.n_items : 1),
                            hipHostMallocDefault));
-    std::map<std::pair<int, int>, std::vector<int>> byshape;
+    // one persistent launch per walker kernel and tuned residency
+    std::map<ClassKey, std::vector<int>> byclass;
     for (int i = 0; i < n; ++i) {
         const labs_step1_cfg& ci = c[i];
         const int L = ci.L, k = (L - 1) / 2;
@@ -259,15 +245,16 @@ labs_status build_plan(const labs_step1_cfg* c, int n, const labs_step1_out* out
         A.traj = outs[i].traj_E;
         A.e_max = -1;
         if (labs_status st_ = set_stamps(A, outs[i])) return st_;
-        const Shape sh = shape_of(L, ci.p);
-        byshape[{sh.NW, sh.R}].push_back(i);
+        const WalkShape ws_ = walk_shape(L, ci.p);
+        const Tile t = tile_override ? *tile_override : tile_for(shape_of(L, ci.p));
+        byclass[{ws_.KH, ws_.NT, ws_.NQ, t.waves}].push_back(i);
     }
     // classes in order of decreasing per-walker cost; inside a class, longest L first
-    std::vector<std::pair<double, std::pair<int, int>>> order;
-    for (auto& kv : byshape) {
+    std::vector<std::pair<double, ClassKey>> order;
+    for (auto& kv : byclass) {
         double cost = 0;
         for (int i : kv.second) {
-            const double w = (double)P->args_h[i].steps_total * P->args_h[i].nf * (kv.first.first + 1);
+            const double w = (double)P->args_h[i].steps_total * P->args_h[i].nf * kv.first[0];
             cost = std::max(cost, w);
         }
         order.push_back({-cost, kv.first});
@@ -276,16 +263,14 @@ labs_status build_plan(const labs_step1_cfg* c, int n, const labs_step1_out* out
     int64_t at = 0;
     const int cus = cu_count();
     for (auto& oc : order) {
-        std::vector<int>& cl = byshape[oc.second];
+        std::vector<int>& cl = byclass[oc.second];
         std::sort(cl.begin(), cl.end(), [&](int a, int b) {
             const double wa = (double)P->args_h[a].steps_total * P->args_h[a].nf;
             const double wb = (double)P->args_h[b].steps_total * P->args_h[b].nf;
             return wa > wb;
         });
-        const Shape sh{oc.second.first, oc.second.second};
-        const Tile t = tile_override ? *tile_override : tile_for(sh);
         WalkKernels wk;
-        if (!walk_kernels_lookup(sh.NW, sh.R, t.RB, &wk)) return invalid("no walker kernel for shape");
+        if (!walk_kernels({oc.second[0], oc.second[1], oc.second[2]}, &wk)) return invalid("no walker kernel for shape");
         ClassRun run;
         run.kern = wk.persistent;
         run.offset = (int)at;
@@ -296,7 +281,7 @@ labs_status build_plan(const labs_step1_cfg* c, int n, const labs_step1_out* out
                 ++cnt;
             }
         run.count = (int)cnt;
-        const int64_t want = (int64_t)cus * 4 * (t.waves > 0 ? t.waves : 2);
+        const int64_t want = (int64_t)cus * 4 * oc.second[3];
         run.grid = (unsigned)std::min<int64_t>(want, cnt > 0 ? cnt : 1);
         P->classes.push_back(run);
         at += cnt;
@@ -331,12 +316,6 @@ labs_status enqueue_plan(const Plan* P, const labs_step1_out* outs, char* base, 
 }
 
 }  // namespace
-
-int walk_tile_rb(int L, int p, int R) {
-    const Shape sh = shape_of(L, p);
-    if (sh.R != R) return R;
-    return tile_for(sh).RB;
-}
 
 size_t batch_workspace_bytes(const labs_step1_cfg* c, int n) { return batch_layout(c, n).total; }
 
@@ -447,27 +426,24 @@ labs_status autotune_step1(const int32_t* Ls, int n_L, int p, int walkers, int s
         labs_step1_out o{};
         o.final_seqs = (uint32_t*)fin;
         o.final_E = (int32_t*)fin + (size_t)walkers * W;
-        std::vector<int> rbs = {sh.R};
-        if ((sh.R + 1) / 2 != sh.R) rbs.push_back((sh.R + 1) / 2);
-        Tile best{sh.R, 2, 1e30};
+        Tile best{sh.R, kDefaultWaves, 1e30};
         hipEvent_t a, b;
         hipEventCreate(&a);
         hipEventCreate(&b);
         labs_status s = LABS_OK;
-        for (int rb : rbs)
-            for (int waves : {1, 2, 3, 4, 8}) {
-                Tile t{rb, waves, 0};
-                s = batch_walk(&c, 1, &o, ws, bl.total, st, &t, false);   // warm-up
-                if (s != LABS_OK) break;
-                hipEventRecord(a, st);
-                s = batch_walk(&c, 1, &o, ws, bl.total, st, &t, false);
-                hipEventRecord(b, st);
-                if (s != LABS_OK) break;
-                hipEventSynchronize(b);
-                float ms = 0;
-                hipEventElapsedTime(&ms, a, b);
-                if (ms < best.ms) best = Tile{rb, waves, ms};
-            }
+        for (int waves : {1, 2, 3, 4, 8}) {
+            Tile t{sh.R, waves, 0};
+            s = batch_walk(&c, 1, &o, ws, bl.total, st, &t, false);   // warm-up
+            if (s != LABS_OK) break;
+            hipEventRecord(a, st);
+            s = batch_walk(&c, 1, &o, ws, bl.total, st, &t, false);
+            hipEventRecord(b, st);
+            if (s != LABS_OK) break;
+            hipEventSynchronize(b);
+            float ms = 0;
+            hipEventElapsedTime(&ms, a, b);
+            if (ms < best.ms) best = Tile{sh.R, waves, ms};
+        }
         hipEventDestroy(a);
         hipEventDestroy(b);
         hipFree(ws);
@@ -511,8 +487,8 @@ labs_status autotune_load(const char* path) {
         if (sscanf(txt.c_str() + pos, "{\"NW\": %d, \"R\": %d, \"RB\": %d, \"waves_per_simd\": %d, \"trial_ms\": %lf",
                    &nw, &r, &rb, &waves, &ms) < 4)
             return invalid("malformed tile table %s", path);
-        WalkKernels wk;
-        if (!walk_kernels_lookup(nw, r, rb, &wk) || wk.RB != rb || waves < 1 || waves > 8)
+        const int re = std::max(r, min_groups(nw));
+        if (nw < 1 || nw > 10 || re > (nw + 1) / 2 + 1 || (rb != re && rb != (re + 1) / 2) || waves < 1 || waves > 8)
             return invalid("tile table %s names an unsupported tile", path);
         tiles[{nw, r}] = Tile{rb, waves, ms};
         ++pos;

@@ -170,6 +170,14 @@ struct WalkArgs {
     int32_t level_E[16];
     unsigned long long* hit_ticks;    // [n_levels], atomic min
     unsigned long long* start_ticks;  // [1], atomic min, stamped by the init kernel
+    // training log (the logging walk only)
+    int32_t* moves;        // [n*steps_total] moved position, or null
+    int32_t* hit;          // [n] first step with E <= e_max, -1: none yet
+    int64_t* evals;        // [n] admissible positions evaluated
+    int32_t log_every, MW;
+    uint32_t* log_seqs;
+    uint32_t* log_mask;
+    int32_t* log_label;
 };
 
 // Stamp every level l that energy E reaches (E <= level_E[l]) with the real-time
@@ -228,8 +236,6 @@ labs_status length_operators(int32_t L, int64_t n, const uint32_t* seqs, uint32_
 labs_status legendre_build(int32_t L, int64_t n_pairs, const int32_t* n_host, const int32_t* o_host,
                            uint32_t* seqs, int32_t* E, void* ws, size_t ws_bytes, hipStream_t st);
 labs_status launch_walker_init_items(const WalkArgs* args, const int2* items, int n_items, hipStream_t st);
-// Autotuned register tile (slots per pass) for the walker of (L, p); R when untuned.
-int walk_tile_rb(int L, int p, int R);
 size_t batch_workspace_bytes(const labs_step1_cfg* c, int n);
 labs_status batch_walk(const labs_step1_cfg* c, int n, const labs_step1_out* outs, void* ws, size_t wsb,
                        hipStream_t st, const void* tile_override, bool use_graph);

@@ -14,25 +14,30 @@
 //   G_a  = sum_m C_{2m} u_m,   Q_a = sum_m u_m^2.
 // The centre a = k+1 flips alone: dC_{2m} = -4 s_a s_{a-2m}.
 //
-// G_a is evaluated bit-sliced.  Forward/backward windows F_a, B_a hold, at bit
-// m-1, the 0/1 digit of s_{a+2m} / s_{a-2m} (0 outside 1..L).  Every C_{2m} is
-// odd (L - 2m terms of +-1), so with C'_m = (C_{2m} - 1)/2 and the two's-complement
-// bit planes P_j of (C'_m)_m,
-//   sum_m C_{2m} F_a(m) = 2 sum_j w_j popcount(P_j & F_a) + popcount(F_a),
-//   w_j = 2^j (sign plane -2^j),
-// and since s = 2*digit - 1 on valid lags,
-//   G_a = 2 (H_f + H_b) - PC[Mf] - PC[Mb] - C_{2mp} s_b,   PC = prefix sums of C_{2m},
-//   Q_a = Mf - 1 + 3 Mb - 4 popcount((F ^ B) & [m <= Mb]) - 2 [mp <= Mb] s_b s_{a-2mp},
-// with Mf = (L-a)/2 and Mb = (a-1)/2 the valid forward/backward lag counts.
-// The planes are built per step with one ballot per (plane, 64 lags); the
-// number of planes is the bit length of max |C'_m| plus the sign, read off the
-// current table each step, so the scan is exact for every state.
+// The class of a position is its parity: cl = 0 holds the odd x, cl = 1 the even x, and
+// index n = (x - 1) >> 1 counts them, so the lag 2m is a step of m indices inside a
+// class.  With x_cl[n] the class (0 outside the sequence), the sum over all lags is
+//   H_a = sum_{n' != n} x_cl[n'] C_{2|n' - n|} = G_a + C_{2mp} s_b,
+// a product of the class with a symmetric Toeplitz matrix of the C table.  It runs on
+// the matrix cores (v_mfma_i32_16x16x64_i8): rows are (class, n mod 8), columns n div 8,
+//   A[(cl, i)][kap] = x_cl[i + kap - kz],   B[kap][j] = C_{2|kap - kz - n0 - 8 j|},
+// so 256 positions take one 16x16 tile and ceil((k+12)/64) products a step, whose
+// operands are aligned LDS reads: eight shifted copies of each class, and one table of
+// the C.  A step changes two elements of the copies and rewrites the table.  C fits a
+// signed byte in all but the first steps of a walk; while some |C| may pass 127 within
+// four steps the bytes above are kept in a second table and multiplied too, so the
+// scan is exact for every state.  By Eq. (2) s_a s_b is constant, and
+//   Q_a = Mf + Mb - 1 + 2 Y_a - 2 s_b s_{a-2mp},   Y_a = sum_m s_{a+2m} s_{a-2m},
+// Mf = (L-a)/2, Mb = (a-1)/2.  Y_a changes with a flip of index f by the one product
+// of f and 2 n_a - f, so it is kept per slot (v_dot4 on the bytes around the flip).
+// At the centre the two halves of H are equal: dE = -4 s_a H + 16 Mb.
 //
-// Windows come from per-parity bit vectors of the sequence: V_pi bit j is the
-// digit of position 2j+2-pi (pi = x & 1, j = (x-1)>>1), VR_pi its reversal over
-// N = 32*NV bits; F_a = V_pi >> (j_a + 1), B_a = VR_pi >> (N - j_a), read with
-// funnel shifts.  Backward windows never need more than NQ = ceil(NW/2) words
-// because Mb <= k/2.
+// What bounds it: instruction issue, about 100 vector and 98 scalar instructions per
+// walker-step at L = 501 on each SIMD, and close behind it the LDS (132 cycles a
+// walker-step per CU, most of them the operands).  The popcount form this replaces
+// needed 915 vector instructions: 16,384 walkers at L = 501, p = 16, 26.7 -> 4.4 us a
+// step (1.44 -> 8.7e11 flip-evaluations/s); L = 301: 14.6 -> 3.8, L = 101: 4.2 -> 3.3,
+// L = 639: 42.5 -> 8.0 us.
 #include "walk_impl.h"
 
 #include <climits>
@@ -49,17 +54,23 @@ using namespace walkimpl;
 
 namespace {
 
-__device__ void walker_init_body(const WalkArgs& A, int64_t j, Lds<10>& S) {
-    constexpr int NW = 10;
+struct InitLds {
+    static constexpr int PADL = 640;            // sv index of position x is PADL + x
+    static constexpr int SV = 1608;
+    int8_t sv[SV];
+    uint32_t pk[32];
+};
+
+__device__ void walker_init_body(const WalkArgs& A, int64_t j, InitLds& S) {
     const int lane = threadIdx.x;
     const int64_t w = A.walker_begin + j;
     const int L = A.L, k = A.k, p = A.p;
     const uint64_t key = walker_key(A.seed, L, w);
     if (A.start_ticks && lane == 0) atomicMin(A.start_ticks, __builtin_amdgcn_s_memrealtime());
     // s_i for i = 1..k+1 from stream outputs i-1; s_1 = +1 when p >= 1; Eq. (2) for the rest
-    for (int i = lane; i < Lds<NW>::SV; i += 64) S.sv[i] = 0;
+    for (int i = lane; i < InitLds::SV; i += 64) S.sv[i] = 0;
     __syncthreads();
-    constexpr int PADL = Lds<NW>::PADL;
+    constexpr int PADL = InitLds::PADL;
     for (int i = 1 + lane; i <= k + 1; i += 64) {
         uint64_t d = sm64_at(key, (uint64_t)(i - 1));
         int s = (d >> 63) ? 1 : -1;
@@ -112,13 +123,13 @@ __device__ void walker_init_body(const WalkArgs& A, int64_t j, Lds<10>& S) {
 }
 
 __global__ __launch_bounds__(64) void k_walker_init(WalkArgs A) {
-    __shared__ Lds<10> S;
+    __shared__ InitLds S;
     walker_init_body(A, blockIdx.x, S);
 }
 
 // Init for a batch of (configuration, walker) items.
 __global__ __launch_bounds__(64) void k_walker_init_items(const WalkArgs* args, const int2* items) {
-    __shared__ Lds<10> S;
+    __shared__ InitLds S;
     const int2 it = items[blockIdx.x];
     const WalkArgs A = args[it.x];
     walker_init_body(A, (int64_t)it.y, S);
@@ -203,19 +214,14 @@ __global__ void k_walk_outputs(WalkArgs A, uint32_t* final_seqs, int32_t* final_
 
 }  // namespace
 
-bool walk_kernels_lookup(int NW, int R, int RB, WalkKernels* out) {
-    if (NW >= 1 && NW <= 4) return walk_kernels_a(NW, R, RB, out);
-    if (NW >= 5 && NW <= 7) return walk_kernels_b(NW, R, RB, out);
-    if (NW >= 8 && NW <= 10) return walk_kernels_c(NW, R, RB, out);
-    return false;
+bool walk_kernels(const WalkShape& s, WalkKernels* out) {
+    if (s.KH <= 8) return s.NT == 1 && s.NQ == 1 && (walk_kernels_a(s.KH, out) || walk_kernels_b(s.KH, out));
+    return walk_kernels_c(s.KH, s.NT, s.NQ, out);
 }
 
 bool walk_shape_supported(int L, int p) {
-    const int k = (L - 1) / 2;
-    const int NW = (k + 31) / 32;
-    const int R = (k + 1 - p + 63) / 64;
     WalkKernels wk;
-    return walk_kernels_lookup(NW, R, R, &wk);
+    return walk_kernels(walk_shape(L, p), &wk);
 }
 
 labs_status launch_walker_init_items(const WalkArgs* args, const int2* items, int n_items, hipStream_t st) {
@@ -238,11 +244,8 @@ labs_status launch_bloom_init(const WalkArgs& A, hipStream_t st) {
 }
 
 labs_status launch_walk(const WalkArgs& A, hipStream_t st) {
-    const int NW = (A.k + 31) / 32;
-    const int R = (A.nf + 63) / 64;
     WalkKernels wk;
-    if (!walk_kernels_lookup(NW, R, walk_tile_rb(A.L, A.p, R), &wk))
-        return invalid("no walker kernel for L=%d p=%d", A.L, A.p);
+    if (!walk_kernels(walk_shape(A.L, A.p), &wk)) return invalid("no walker kernel for L=%d p=%d", A.L, A.p);
     if (A.bloom) {
         const size_t lds = sizeof(uint32_t) << (A.bloom_log2 - 5);
         hipLaunchKernelGGL(wk.bloom, dim3((unsigned)A.n), dim3(64), lds, st, A);

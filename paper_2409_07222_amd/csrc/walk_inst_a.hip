@@ -1,54 +1,23 @@
-// Instantiations of the first-step walker for NW in {1, 2, 3, 4}.
+// Instantiations of the first-step walker for KH in 2..5.
 #include "walk_impl.h"
 
 namespace labsdev {
 
 namespace {
-template <int NW, int R, int RB>
+template <int KH, int NT, int NQ>
 void fill(WalkKernels* o) {
-    o->plain = walkimpl::k_walk<NW, R, RB>;
-    o->bloom = walkimpl::k_walk_bloom<NW, R, RB>;
-    o->persistent = walkimpl::k_walk_persistent<NW, R, RB>;
-    o->R = R;
-    o->RB = RB;
-}
-
-template <int NW, int R>
-void fill_rb(int RB, WalkKernels* o) {
-    constexpr int H = (R + 1) / 2;
-    if (RB < R) fill<NW, R, H>(o); else fill<NW, R, R>(o);
-}
-
-// Slot groups R (64 free positions each) in {ceil(NW/2) - 1, ceil(NW/2),
-// ceil(NW/2) + 1}: with k in (32(NW-1), 32NW] and the prefixes in use these hold
-// R = ceil((k+1-p)/64) exactly, so no group of 64 slots is scanned for nothing;
-// a smaller R (a long prefix) runs in the smallest group count.  RB in {R, ceil(R/2)}.
-template <int NW>
-bool pick(int R, int RB, WalkKernels* o) {
-    constexpr int R0 = (NW + 1) / 2;
-    constexpr int Rm = R0 > 1 ? R0 - 1 : 1;
-    if (R <= Rm) {
-        fill_rb<NW, Rm>(RB, o);
-        return true;
-    }
-    if (R == R0) {
-        fill_rb<NW, R0>(RB, o);
-        return true;
-    }
-    if (R == R0 + 1) {
-        fill_rb<NW, R0 + 1>(RB, o);
-        return true;
-    }
-    return false;
+    o->plain = walkimpl::k_walk<KH, NT, NQ>;
+    o->bloom = walkimpl::k_walk_bloom<KH, NT, NQ>;
+    o->persistent = walkimpl::k_walk_persistent<KH, NT, NQ>;
 }
 }  // namespace
 
-bool walk_kernels_a(int NW, int R, int RB, WalkKernels* o) {
-    switch (NW) {
-        case 1: return pick<1>(R, RB, o);
-        case 2: return pick<2>(R, RB, o);
-        case 3: return pick<3>(R, RB, o);
-        case 4: return pick<4>(R, RB, o);
+bool walk_kernels_a(int KH, WalkKernels* o) {
+    switch (KH) {
+        case 2: fill<2, 1, 1>(o); return true;
+        case 3: fill<3, 1, 1>(o); return true;
+        case 4: fill<4, 1, 1>(o); return true;
+        case 5: fill<5, 1, 1>(o); return true;
         default: return false;
     }
 }

@@ -1,55 +1,35 @@
-// Instantiations of the first-step walker for NW in {8, 9, 10}.
+// Instantiations of the first-step walker for KH in 9..11.
 #include "walk_impl.h"
 
 namespace labsdev {
 
 namespace {
-template <int NW, int R, int RB>
+template <int KH, int NT, int NQ>
 void fill(WalkKernels* o) {
-    o->plain = walkimpl::k_walk<NW, R, RB>;
-    o->bloom = walkimpl::k_walk_bloom<NW, R, RB>;
-    o->persistent = walkimpl::k_walk_persistent<NW, R, RB>;
-    o->R = R;
-    o->RB = RB;
-}
-
-template <int NW, int R>
-void fill_rb(int RB, WalkKernels* o) {
-    constexpr int H = (R + 1) / 2;
-    if (RB < R) fill<NW, R, H>(o); else fill<NW, R, R>(o);
-}
-
-// Slot groups R (64 free positions each) in {ceil(NW/2) - 1, ceil(NW/2),
-// ceil(NW/2) + 1}: with k in (32(NW-1), 32NW] and the prefixes in use these hold
-// R = ceil((k+1-p)/64) exactly, so no group of 64 slots is scanned for nothing;
-// a smaller R (a long prefix) runs in the smallest group count.  RB in {R, ceil(R/2)}.
-template <int NW>
-bool pick(int R, int RB, WalkKernels* o) {
-    constexpr int R0 = (NW + 1) / 2;
-    constexpr int Rm = R0 > 1 ? R0 - 1 : 1;
-    if (R <= Rm) {
-        fill_rb<NW, Rm>(RB, o);
-        return true;
-    }
-    if (R == R0) {
-        fill_rb<NW, R0>(RB, o);
-        return true;
-    }
-    if (R == R0 + 1) {
-        fill_rb<NW, R0 + 1>(RB, o);
-        return true;
-    }
-    return false;
+    o->plain = walkimpl::k_walk<KH, NT, NQ>;
+    o->bloom = walkimpl::k_walk_bloom<KH, NT, NQ>;
+    o->persistent = walkimpl::k_walk_persistent<KH, NT, NQ>;
 }
 }  // namespace
 
-bool walk_kernels_c(int NW, int R, int RB, WalkKernels* o) {
-    switch (NW) {
-        case 8: return pick<8>(R, RB, o);
-        case 9: return pick<9>(R, RB, o);
-        case 10: return pick<10>(R, RB, o);
-        default: return false;
+bool walk_kernels_c(int KH, int NT, int NQ, WalkKernels* o) {
+    if (KH == 9 && NQ == 1) {
+        if (NT == 1) fill<9, 1, 1>(o); else fill<9, 2, 1>(o);
+        return true;
     }
+    if (KH == 9 && NQ == 2) {
+        if (NT == 1) fill<9, 1, 2>(o); else fill<9, 2, 2>(o);
+        return true;
+    }
+    if (KH == 10 && NQ == 2) {
+        if (NT == 1) fill<10, 1, 2>(o); else fill<10, 2, 2>(o);
+        return true;
+    }
+    if (KH == 11 && NQ == 2) {
+        if (NT == 1) fill<11, 1, 2>(o); else fill<11, 2, 2>(o);
+        return true;
+    }
+    return false;
 }
 
 }  // namespace labsdev

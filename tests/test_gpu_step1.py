@@ -279,3 +279,55 @@ def test_pool_topk_and_walker_best(lb, orc):
     s, E = lb.pool_topk(pool, 10)
     assert [int(e) for e in E.cpu().numpy()] == [e for e, _ in ref[:10]]
     assert [orc.seq_key(x) for x in _host_seqs(s, L)] == [k for _, k in ref[:10]]
+
+
+# ------------------------------------------------------------------ edges of the walk kernel
+# Lengths on both sides of every size the matrix-core scan is instantiated at: the class
+# rows grow by 32 indices where k + 12 passes a multiple of 32 (L = 105/107, 169/171, ...,
+# 617/619), a second group of lags starts at k > 256 (L = 513/515), a second tile of slots
+# where more than 128 indices are scanned (p = 0 against p = 16 from L = 511 on), and long
+# prefixes leave two free positions.  Even and odd k read the partner lags differently.
+_EDGES = [(5, 0), (7, 1), (9, 0), (31, 0), (33, 2), (105, 0), (107, 0), (169, 3), (171, 1), (233, 12), (235, 12),
+          (297, 12), (299, 5), (361, 1), (363, 12), (425, 16), (427, 2), (489, 16), (491, 7), (501, 0), (501, 248),
+          (509, 0), (511, 16), (513, 16), (513, 255), (515, 2), (515, 17), (527, 8), (527, 0), (553, 2), (553, 40),
+          (555, 1), (617, 16), (617, 0), (619, 0), (619, 60), (637, 1), (639, 0), (639, 16), (639, 317)]
+
+
+@pytest.mark.parametrize("L,p", _EDGES)
+def test_walk_scan_edges(lb, orc, L, p):
+    nf = (L - 1) // 2 + 1 - p
+    hi = min(L // 5, nf - 1)
+    lo = min(L // 10, hi)
+    n, steps = 40, 150
+    r = lb.walk_step1(L, p, steps, lo, hi, 70 + L, n, want_traj=True)
+    o = orc.baseline_walk(L, p, steps, lo, hi, 70 + L, 0, n, want_traj=True)
+    assert np.array_equal(r.traj_E.cpu().numpy(), o["traj"])
+    assert np.array_equal(r.best_E.cpu().numpy(), o["best_E"])
+    # the packed results, rebuilt from the class rows, carry these energies
+    for seqs, E in ((r.final_seqs, r.final_E), (r.best_seqs, r.best_E)):
+        assert np.array_equal(orc.energy_batch(_host_seqs(seqs, L)), E.cpu().numpy())
+
+
+@pytest.mark.parametrize("L,p", [(105, 0), (301, 12), (513, 16), (515, 2), (527, 0), (553, 2), (619, 16)])
+def test_bloom_scan_edges(lb, orc, L, p):
+    steps, n = 12, 2
+    r = lb.walk_step1(L, p, steps, 0, 0, 5 + L, n, want_traj=True, bloom=(10, 5))
+    o = orc.walk_bloom(L, p, steps, 10, 5, 5 + L, range(n))
+    assert np.array_equal(r.traj_E.cpu().numpy(), o["traj"])
+
+
+def test_batched_scan_edges(lb):
+    """The persistent form at the same edges, against one launch per length."""
+    import torch
+    cfgs = []
+    for L, p in _EDGES:
+        nf = (L - 1) // 2 + 1 - p
+        hi = min(L // 5, nf - 1)
+        cfgs.append(dict(L=L, p=p, steps=90, tenure_lo=min(L // 10, hi), tenure_hi=hi, seed=9, n_walkers=24))
+    res, _ = lb.walk_step1_batch(cfgs, want_traj=True)
+    torch.cuda.synchronize()
+    for c, r in zip(cfgs, res):
+        one = lb.walk_step1(c["L"], c["p"], c["steps"], c["tenure_lo"], c["tenure_hi"], c["seed"], c["n_walkers"],
+                            want_traj=True)
+        assert torch.equal(r.traj_E, one.traj_E), (c["L"], c["p"])
+        assert torch.equal(r.best_seqs, one.best_seqs) and torch.equal(r.final_seqs, one.final_seqs), (c["L"], c["p"])
