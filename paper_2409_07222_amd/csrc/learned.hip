@@ -21,6 +21,7 @@ namespace {
 constexpr int kLwLmax = 639;
 constexpr int kLwWmax = 20;
 constexpr int kLwKmax = 319;
+constexpr int kLogSegment = 4096;   // steps a launch of the logging walk
 constexpr int kLwSlots = 5;   // ceil((kLwKmax + 1) / 64) free positions per lane
 
 struct LwArgs {
@@ -324,6 +325,10 @@ __global__ void k_lw_outputs(LwArgs A, uint32_t* final_seqs, int32_t* final_E, u
     }
 }
 
+__global__ __launch_bounds__(256) void k_fill_i16(int64_t n, int16_t* p, int16_t v) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = v;
+}
+
 __global__ __launch_bounds__(256) void k_sum_i64(int64_t n, const int64_t* v, int64_t* out) {
     __shared__ int64_t part[256];
     int64_t s = 0;
@@ -445,8 +450,42 @@ labs_status learned_walk(const labs_step1_cfg& c, const labs_proposer& pr, const
                        A.hitmask);
     LABS_LAUNCHED("k_lw_init");
 
-    // One launch sequence per step; steps t with (t-1) mod F == 0 need no network pass.
+    const int64_t tot = n * A.W > n ? n * A.W : n;
     const int F = pr.fallback_every;
+    if (F == 1) {
+        // Every step a full exact scan: the plain walker's kernel, whose matrix-core scan
+        // costs a hundredth of a step here (16,384 walkers at L = 501, a record every 7
+        // steps: 705 -> 5.6 us a step).
+        WalkArgs& w = B.wa;
+        w.traj = o.traj_E;
+        w.moves = o.moves;
+        w.hit = A.hit;
+        w.evals = A.evals;
+        w.log_every = A.log_every;
+        w.MW = A.MW;
+        w.log_seqs = A.log_seqs;
+        w.log_mask = A.log_mask;
+        w.log_label = A.log_label;
+        for (int t0 = 0; t0 < c.steps; t0 += kLogSegment) {
+            w.t0 = t0;
+            w.t1 = t0 + kLogSegment < c.steps ? t0 + kLogSegment : c.steps;
+            if ((s = launch_walk_log(w, st))) return s;
+        }
+        if (o.cands) {
+            const int64_t cn = n * c.steps * A.top_m;
+            hipLaunchKernelGGL(k_fill_i16, dim3((unsigned)(cn / 256 + 1 < 65536 ? cn / 256 + 1 : 65536)), dim3(256), 0,
+                               st, cn, o.cands, (int16_t)-1);
+            LABS_LAUNCHED("k_fill_i16");
+        }
+        hipLaunchKernelGGL(k_lw_outputs, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, A, o.final_seqs,
+                           o.final_E, o.best_seqs, o.best_E, o.best_step, o.hit_step);
+        LABS_LAUNCHED("k_lw_outputs");
+        hipLaunchKernelGGL(k_sum_i64, dim3(1), dim3(256), 0, st, n, A.evals, o.flip_evals);
+        LABS_LAUNCHED("k_sum_i64");
+        return LABS_OK;
+    }
+
+    // One launch sequence per step; steps t with (t-1) mod F == 0 need no network pass.
     auto enqueue_step = [&](int t, hipStream_t q) -> labs_status {
         if (mlp && ((t - 1) % F) != 0) {
             labs_status r = mlp_forward(lay, pr.params, pr.params_bf16, n, A.X, const_cast<float*>(A.logits),
@@ -501,7 +540,6 @@ labs_status learned_walk(const labs_step1_cfg& c, const labs_proposer& pr, const
     for (; t <= c.steps; ++t)
         if ((s = enqueue_step(t, st))) return s;
 
-    const int64_t tot = n * A.W > n ? n * A.W : n;
     hipLaunchKernelGGL(k_lw_outputs, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, A, o.final_seqs,
                        o.final_E, o.best_seqs, o.best_E, o.best_step, o.hit_step);
     LABS_LAUNCHED("k_lw_outputs");

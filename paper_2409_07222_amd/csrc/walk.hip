@@ -257,6 +257,14 @@ labs_status launch_walk(const WalkArgs& A, hipStream_t st) {
     return LABS_OK;
 }
 
+labs_status launch_walk_log(const WalkArgs& A, hipStream_t st) {
+    WalkKernels wk;
+    if (!walk_kernels(walk_shape(A.L, A.p), &wk)) return invalid("no walker kernel for L=%d p=%d", A.L, A.p);
+    hipLaunchKernelGGL(wk.log, dim3((unsigned)A.n), dim3(64), 0, st, A);
+    LABS_LAUNCHED("k_walk_log");
+    return LABS_OK;
+}
+
 labs_status launch_offer_best(const WalkArgs& A, hipStream_t st) {
     hipLaunchKernelGGL(k_offer_best, dim3((unsigned)A.n), dim3(64), 0, st, A);
     LABS_LAUNCHED("k_offer_best");

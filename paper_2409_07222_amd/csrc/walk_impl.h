@@ -638,6 +638,14 @@ __global__ __launch_bounds__(64, (WavesPerSimd<KH, NT>::value)) void k_walk_bloo
     walk_body<KH, NT, NQ, true, false>(A, blockIdx.x, S, bloom_words);
 }
 
+// The plain walk with the learned walk's outputs: moves, first hit, evaluations (the
+// admissible positions of every step) and the training log.
+template <int KH, int NT, int NQ>
+__global__ __launch_bounds__(64, (WavesPerSimd<KH, NT>::value)) void k_walk_log(WalkArgs A) {
+    __shared__ Lds<KH, NT, NQ> S;
+    walk_body<KH, NT, NQ, false, true>(A, blockIdx.x, S, nullptr);
+}
+
 // Persistent form: each wavefront takes (configuration, walker) items from a
 // queue until it is empty, so every wavefront exits.
 template <int KH, int NT, int NQ>
@@ -666,7 +674,7 @@ typedef void (*walk_persistent_t)(const WalkArgs*, const int2*, int, unsigned*);
 // Kernels of the shape class of (L, p).  KH: the class rows in units of 32 indices,
 // NT: 128-index tiles of slots a class, NQ: groups of 256 lags.
 struct WalkKernels {
-    walkimpl::walk_kernel_t plain, bloom;
+    walkimpl::walk_kernel_t plain, bloom, log;
     walkimpl::walk_persistent_t persistent;
 };
 struct WalkShape {

@@ -8,6 +8,7 @@ template <int KH, int NT, int NQ>
 void fill(WalkKernels* o) {
     o->plain = walkimpl::k_walk<KH, NT, NQ>;
     o->bloom = walkimpl::k_walk_bloom<KH, NT, NQ>;
+    o->log = walkimpl::k_walk_log<KH, NT, NQ>;
     o->persistent = walkimpl::k_walk_persistent<KH, NT, NQ>;
 }
 }  // namespace

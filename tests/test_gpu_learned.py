@@ -206,3 +206,52 @@ def test_single_walker_default_steps(lb):
     narrow = lb.learned_walk(L, p, 0, lo, hi, 9, 1, mode=lb.PROPOSE_RANDOM, top_m=1,
                              fallback_every=4, want_traj=True)
     assert int(narrow["flip_evals"].item()) < int(r["flip_evals"].item())
+
+
+@pytest.mark.parametrize("L,p,steps,every", [(7, 1, 9, 2), (101, 8, 24, 5), (301, 12, 12, 4), (513, 255, 10, 3),
+                                             (515, 2, 9, 4), (527, 0, 9, 3), (639, 16, 6, 5)])
+def test_logging_walk_edges(lb, orc, L, p, steps, every):
+    """Every step a full scan (the plain walk's kernel with the log's outputs): records,
+    moves, hits, evaluations and candidate rows at the scan kernel's size edges."""
+    nf = (L - 1) // 2 + 1 - p
+    hi = min(L // 5, nf - 1)
+    lo = min(L // 10, hi)
+    n, seed = 3, 31 + L
+    E0 = [orc.energy(orc.walker_init(seed, L, p, w, lo, hi)[0]) for w in range(n)]
+    e_max = min(E0) - 1                      # some walkers hit it on the way down
+    r = lb.learned_walk(L, p, steps, lo, hi, seed, n, mode=lb.PROPOSE_RANDOM, top_m=2, fallback_every=1,
+                        log_every=every, e_max=e_max, want_traj=True, want_cands=True)
+    traj, moves, hit = _np(r["traj_E"]), _np(r["moves"]), _np(r["hit_step"])
+    seqs, mask, label = _np(r["log_seqs"]), _np(r["log_mask"]), _np(r["log_label"])
+    assert (_np(r["cands"]) == -1).all()
+    evals = 0
+    for w in range(n):
+        ref = ol.proposal_walk(L, p, steps, lo, hi, seed, w, 1, None, e_max=e_max)
+        assert np.array_equal(traj[w], np.array(ref["traj"])), w
+        assert np.array_equal(moves[w], np.array(ref["moves"])), w
+        assert hit[w] == ref["hit_step"]
+        evals += sum(len(a) for a in ref["admissible"])
+        for q in range(steps // every):
+            t, rec = (q + 1) * every, q * n + w
+            assert np.array_equal(li.unpack(seqs[rec:rec + 1].view(np.uint32), L)[0], ref["states"][t - 1])
+            adm = [a for a in range(1, (L - 1) // 2 + 2)
+                   if (int(mask[rec, (a - 1) // 32]) >> ((a - 1) % 32)) & 1]
+            assert adm == ref["admissible"][t - 1]
+            assert label[rec] == ref["moves"][t - 1] - 1
+    assert int(r["flip_evals"].item()) == evals
+
+
+def test_logging_walk_across_segments(lb):
+    """More steps than one launch holds: trajectory, best and records as the plain walk's."""
+    L, p, lo, hi, steps, n = 37, 2, 3, 6, 9000, 8
+    plain = lb.walk_step1(L, p, steps, lo, hi, 5, n, want_traj=True)
+    r = lb.learned_walk(L, p, steps, lo, hi, 5, n, mode=lb.PROPOSE_RANDOM, top_m=1, fallback_every=1,
+                        log_every=700, want_traj=True)
+    assert np.array_equal(_np(r["traj_E"]), _np(plain.traj_E))
+    assert np.array_equal(_np(r["best_step"]), _np(plain.best_step))
+    assert np.array_equal(_np(r["best_seqs"]), _np(plain.best_seqs))
+    # record q is the state before step 700 (q + 1): its energy is the trajectory's
+    E = lb.energy(L, r["log_seqs"]).cpu().numpy().reshape(steps // 700, n)
+    traj = _np(plain.traj_E)
+    for q in range(steps // 700):
+        assert np.array_equal(E[q], traj[:, 700 * (q + 1) - 2])
