@@ -485,11 +485,15 @@ labs_status learned_walk(const labs_step1_cfg& c, const labs_proposer& pr, const
         return LABS_OK;
     }
 
+    const bool packed = mlp && mlp_packs(lay);
+    if (packed && (s = mlp_pack(lay, pr.params_bf16, B.fwd_ws, B.fwd_bytes, st))) return s;
+
     // One launch sequence per step; steps t with (t-1) mod F == 0 need no network pass.
     auto enqueue_step = [&](int t, hipStream_t q) -> labs_status {
         if (mlp && ((t - 1) % F) != 0) {
-            labs_status r = mlp_forward(lay, pr.params, pr.params_bf16, n, A.X, const_cast<float*>(A.logits),
-                                        B.fwd_ws, B.fwd_bytes, q);
+            labs_status r = packed ? mlp_forward_packed(lay, pr.params, B.fwd_ws, n, A.X, const_cast<float*>(A.logits), q)
+                                   : mlp_forward(lay, pr.params, pr.params_bf16, n, A.X, const_cast<float*>(A.logits),
+                                                 B.fwd_ws, B.fwd_bytes, q);
             if (r) return r;
         }
         hipLaunchKernelGGL(k_lw_step, dim3((unsigned)n), dim3(64), 0, q, A);

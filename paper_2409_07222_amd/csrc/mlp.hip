@@ -9,25 +9,12 @@
 
 #include <cmath>
 
-namespace labsdev {
+#include "mlp_tile.h"
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+namespace labsdev {
 
 // ------------------------------------------------------------------ scalars
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-// GELU, tanh form (Hendrycks and Gimpel 2016), and its derivative.
-__device__ __forceinline__ float gelu_f(float x) {
-    const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-    return 0.5f * x * (1.0f + tanhf(u));
-}
-__device__ __forceinline__ float gelu_grad_f(float x) {
-    const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-    const float t = tanhf(u);
-    const float du = 0.7978845608028654f * (1.0f + 3.0f * 0.044715f * x * x);
-    return 0.5f * (1.0f + t) + 0.5f * x * (1.0f - t * t) * du;
-}
 
 // ------------------------------------------------------------------ GEMM
 // C[m][n] = sum_k A(m,k) B(k,n) over bf16 operands with FP32 accumulation.
@@ -562,13 +549,177 @@ labs_status launch_features(int L, int64_t n, const uint32_t* seqs, uint16_t* X,
     return LABS_OK;
 }
 
+// ------------------------------------------------------------------ forward pass
+// Packs W1, W2 and W3 into fragment order (zeros beyond each layer's rows and columns).
+__global__ __launch_bounds__(256) void k_pack_weights(labs_mlp_layout y, const uint16_t* __restrict__ Pb,
+                                                      uint16_t* __restrict__ out) {
+    const int64_t n1 = packed_elems(y.hidden, y.d_in) / 8, n2 = packed_elems(y.hidden, y.hidden) / 8,
+                  n3 = packed_elems(y.d_out, y.hidden) / 8;
+    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n1 + n2 + n3) return;     // the slack behind is read, never used
+    uint4* const dst = (uint4*)out + i;
+    const uint16_t* W = Pb + y.off_W1;
+    int rows = y.hidden, K = y.d_in, ld = y.ld_in;
+    if (i >= n1 + n2) {
+        i -= n1 + n2;
+        W = Pb + y.off_W3;
+        rows = y.d_out;
+        K = ld = y.hidden;
+    } else if (i >= n1) {
+        i -= n1;
+        W = Pb + y.off_W2;
+        K = ld = y.hidden;
+    }
+    const int nch = (K + 31) / 32;
+    const int lane = (int)(i & 63), kc = (int)((i >> 6) % nch), t = (int)((i >> 6) / nch);
+    const int row = 16 * t + (lane & 15), k = 32 * kc + 8 * (lane >> 4);
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (row < rows && k < K) {
+        v = *(const uint4*)(W + (int64_t)row * ld + k);
+        if (k + 8 > K) v = mask_tail(v, k, K);
+    }
+    *dst = v;
+}
+
+// The three layers of 16 MR rows by one workgroup: the feature rows and the hidden
+// activations stay in LDS, the packed weights are read from the L2 (655 KB a workgroup
+// at L = 501, hidden 256).  Bound by the latency of those loads and of the operand reads
+// from LDS, with GELU and the rows' first load behind; the products themselves take 3 us.
+// As three launches of tiled products the activations went through memory and the narrow
+// layers left CUs idle: 16,384 rows at L = 501, hidden 256, 62.9 -> 29.7 us with the
+// packing (4 us), 100 rows 34.0 -> 17.2.
+struct FwdArgs {
+    int n, d_in, ld_in, hidden, d_out, ld_out;
+    const uint16_t *X, *W1, *W2, *W3;   // W*: packed
+    const float *b1, *b2, *b3;
+    float* logits;
+};
+
+// LDS of a workgroup of 16 MR rows: the features or the second hidden layer, the first
+// hidden layer, one step of reads past the end.
+__host__ __device__ inline int forward_lds(int mr, int ld_in, int hidden) {
+    const int sx = tile_stride(ld_in), sh = tile_stride(hidden);
+    return 16 * mr * ((sx > sh ? sx : sh) + sh) + 64;
+}
+
+template <int MR>
+__global__ __launch_bounds__(kTileThreads, MR == 4 ? 2 : 4) void k_forward(FwdArgs F) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int ROWS = 16 * MR;
+    const int sx = tile_stride(F.ld_in), sh = tile_stride(F.hidden);
+    char* const X = lds;                 // the second hidden layer takes its place
+    char* const H1 = lds + ROWS * (sx > sh ? sx : sh);
+    const int64_t m0 = (int64_t)blockIdx.x * ROWS;
+    // a wave a row, 16 bytes a lane; RW rows in flight
+    const int per = F.ld_in / 8, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int RW = ROWS / kTileWaves;
+    for (int c = lane; c < per; c += 64) {
+        uint4 v[RW];
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int64_t r = m0 + wave + kTileWaves * i;
+            v[i] = *(const uint4*)(F.X + (r < F.n ? r : F.n - 1) * F.ld_in + 8 * c);   // rows past n are not stored
+        }
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            if (8 * c + 8 > F.d_in) v[i] = mask_tail(v[i], 8 * c, F.d_in);
+            *(uint4*)(X + (wave + kTileWaves * i) * sx + 16 * c) = v[i];
+        }
+    }
+    __syncthreads();
+    tile_layer<MR>(X, sx, F.W1, F.b1, F.hidden, F.d_in,
+                   [&](int col, int row, const float (&b)[4], f32x4 v) { store_hidden(H1, sh, b, col, row, v); });
+    __syncthreads();
+    tile_layer<MR>(H1, sh, F.W2, F.b2, F.hidden, F.hidden,
+                   [&](int col, int row, const float (&b)[4], f32x4 v) { store_hidden(X, sh, b, col, row, v); });
+    __syncthreads();
+    tile_layer<MR>(X, sh, F.W3, F.b3, F.d_out, F.hidden, [&](int col, int row, const float (&b)[4], f32x4 v) {
+        if (m0 + row >= F.n) return;
+        float* z = F.logits + (m0 + row) * F.ld_out + col;
+        if (col + 3 < F.d_out) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z[j] = v[j] + b[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (col + j < F.d_out) z[j] = v[j] + b[j];
+        }
+    });
+}
+
+constexpr int kLdsBytes = 160 * 1024;
+// Widest hidden layer of the one-workgroup kernel: beyond it two layers' rows no longer
+// leave room for a second workgroup at L = 501, and the separate products' tiles are full.
+constexpr int kFusedHidden = 256;
+
+static int64_t packed_total(const labs_mlp_layout& y) {
+    return packed_elems(y.hidden, y.d_in) + packed_elems(y.hidden, y.hidden) + packed_elems(y.d_out, y.hidden) +
+           512 * kTilePF;
+}
+
+// Row tiles a workgroup.  While one workgroup a CU holds every row, the fewest tiles that
+// do (L = 501, hidden 256: 4,096 rows 17.5 us at one, 19.4 at two, 25.2 at four; 8,192
+// rows 25.8, 21.3, 26.7).  Beyond, four tiles read each weight least often but leave one
+// workgroup a CU, so a last round that is at most half full costs more than it saves:
+// 16,384 rows 33.0 us at two and 29.7 at four, 20,480 rows 44.9 and 49.7.
+static int forward_tiles(const labs_mlp_layout& y, int64_t n) {
+    constexpr int kCUs = 256;
+    const int64_t last = (n + 63) / 64 % kCUs;
+    int mr = n <= 16 * kCUs ? 1 : n <= 32 * kCUs || (last > 0 && last <= kCUs / 2) ? 2 : 4;
+    while (mr > 1 && forward_lds(mr, y.ld_in, y.hidden) > kLdsBytes) mr /= 2;
+    return mr;
+}
+
+template <int MR>
+static labs_status run_forward(const FwdArgs& F, hipStream_t st) {
+    const int bytes = forward_lds(MR, F.ld_in, F.hidden);
+    LABS_HIP(hipFuncSetAttribute((const void*)k_forward<MR>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes));
+    hipLaunchKernelGGL(k_forward<MR>, dim3((unsigned)((F.n + 16 * MR - 1) / (16 * MR))), dim3(kTileThreads), bytes, st,
+                       F);
+    LABS_LAUNCHED("k_forward");
+    return LABS_OK;
+}
+
+bool mlp_packs(const labs_mlp_layout& y) { return y.hidden <= kFusedHidden; }
+
+labs_status mlp_pack(const labs_mlp_layout& y, const uint16_t* Pb, void* ws, size_t wsb, hipStream_t st) {
+    if (wsb < (size_t)packed_total(y) * 2) return LABS_E_NOMEM;
+    hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)((packed_total(y) / 8 + 255) / 256)), dim3(256), 0, st, y, Pb,
+                       (uint16_t*)ws);
+    LABS_LAUNCHED("k_pack_weights");
+    return LABS_OK;
+}
+
+labs_status mlp_forward_packed(const labs_mlp_layout& y, const float* P, const void* ws, int64_t n, const uint16_t* X,
+                               float* logits, hipStream_t st) {
+    if (n <= 0) return LABS_OK;
+    const uint16_t* W1 = (const uint16_t*)ws;
+    const uint16_t* W2 = W1 + packed_elems(y.hidden, y.d_in);
+    const uint16_t* W3 = W2 + packed_elems(y.hidden, y.hidden);
+    const FwdArgs F{(int)n, y.d_in, y.ld_in, y.hidden, y.d_out, y.ld_out, X, W1, W2, W3, P + y.off_b1, P + y.off_b2,
+                    P + y.off_b3, logits};
+    switch (forward_tiles(y, n)) {
+        case 4: return run_forward<4>(F, st);
+        case 2: return run_forward<2>(F, st);
+        default: return run_forward<1>(F, st);
+    }
+}
+
 size_t mlp_forward_ws(const labs_mlp_layout& y, int64_t n) {
+    if (mlp_packs(y)) return (size_t)packed_total(y) * 2 + 256;
     return 2 * align_up((size_t)n * y.hidden * 2, 256) + 256;
 }
 
 labs_status mlp_forward(const labs_mlp_layout& y, const float* P, const uint16_t* Pb, int64_t n, const uint16_t* X,
                         float* logits, void* ws, size_t wsb, hipStream_t st) {
     if (n <= 0) return LABS_OK;
+    if (mlp_packs(y)) {
+        Carve cv(ws, wsb);
+        uint16_t* wp = cv.take<uint16_t>((size_t)packed_total(y));
+        if (!wp) return LABS_E_NOMEM;
+        if (labs_status s = mlp_pack(y, Pb, wp, (size_t)packed_total(y) * 2, st)) return s;
+        return mlp_forward_packed(y, P, wp, n, X, logits, st);
+    }
     Carve cv(ws, wsb);
     uint16_t* h1 = cv.take<uint16_t>((size_t)n * y.hidden);
     uint16_t* h2 = cv.take<uint16_t>((size_t)n * y.hidden);

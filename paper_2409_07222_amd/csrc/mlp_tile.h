@@ -1,0 +1,180 @@
+// Device pieces of the network kernels that keep a tile of rows in LDS through
+// several layers (the forward pass, the training pass, the learned walk's step).
+#pragma once
+#include "labs_internal.h"
+
+#include <type_traits>
+
+namespace labsdev {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// GELU, tanh form (Hendrycks and Gimpel 2016), and its derivative.
+__device__ __forceinline__ float gelu_f(float x) {
+    const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
+    return 0.5f * x * (1.0f + tanhf(u));
+}
+__device__ __forceinline__ float gelu_grad_f(float x) {
+    const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
+    const float t = tanhf(u);
+    const float du = 0.7978845608028654f * (1.0f + 3.0f * 0.044715f * x * x);
+    return 0.5f * (1.0f + t) + 0.5f * x * (1.0f - t * t) * du;
+}
+
+// bf16(gelu_f(x)) of four values.  x (1 - 1 / (1 + e^{2u})) from the hardware exponential
+// and reciprocal lies within 1e-6 |x| of gelu_f's value (both are within 5e-7 |x| of the
+// true one: tanhf and the sum 1 + tanh err by a few 2^-24, the exponential by
+// 2^-23 + |2u| 2^-24 of its value, which the slope of 1 / (1 + e) makes at most 0.45
+// 2^-23); where the two ends of that interval round to the same bf16, so does gelu_f's.
+// The few others (about one value in a thousand), infinities and NaN take gelu_f itself,
+// which branches per value and leaves no two of them in flight.
+__device__ __forceinline__ void gelu_bf16(const float (&x)[4], uint32_t (&h)[4]) {
+    uint32_t far = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float u = 0.7978845608028654f * (x[j] + 0.044715f * x[j] * x[j] * x[j]);
+        const float q = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(2.8853900817779268f * u));
+        const float r = x[j] - x[j] * q;
+        const float d = 1e-6f * fabsf(x[j]);
+        h[j] = f2bf(r - d);
+        far |= (h[j] ^ f2bf(r + d)) | (fabsf(x[j]) < 1e4f ? 0u : 1u);
+    }
+    if (far) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) h[j] = f2bf(gelu_f(x[j]));
+    }
+}
+
+// Zeroes the elements of an 8-element bf16 chunk that start at index k and reach K.
+__device__ __forceinline__ uint4 mask_tail(uint4 v, int k, int K) {
+    uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (k + 2 * j >= K) w[j] = 0;
+        else if (k + 2 * j + 1 >= K) w[j] &= 0xFFFFu;
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Weights in fragment order: of column tile t (16 rows of W) and step kc (32 columns),
+// lane l's 16 bytes are W[16 t + l % 16][32 kc + 8 (l / 16) .. + 7], so a wave's operand is
+// one contiguous kilobyte (rows of W themselves would touch 64 cache lines).
+__host__ __device__ inline int64_t packed_elems(int ncols, int K) {
+    return (int64_t)((ncols + 15) / 16) * ((K + 31) / 32) * 512;
+}
+
+// A workgroup is 8 waves over 16 MR rows; a wave takes every row and two column tiles at
+// a time, so each weight is read once a workgroup and each fragment of the rows feeds
+// two products.
+constexpr int kTileThreads = 512;
+constexpr int kTileWaves = kTileThreads / 64;
+constexpr int kTilePF = 4;
+
+// acc[c][r] = (16 columns of tile t[c]) (tile rows 16 r .. + 15)^T over the steps of K, in
+// order: the layer's columns are the matrix product's rows, so a lane ends with four
+// consecutive columns 4 (lane / 16) .. + 3 of row lane % 16.  A: the rows in LDS, stride
+// sa bytes.  WP: packed weights, nch steps a tile, read PF steps ahead: past a tile's end
+// the reads run on into what follows (kTilePF steps of slack after the last layer, one
+// step after the rows in LDS) and are not used.
+template <int MR, int CT>
+__device__ __forceinline__ void tile_product(f32x4 (&acc)[CT][MR], const char* A, int sa, const uint16_t* __restrict__ WP,
+                                             const int (&t)[CT], int nch) {
+    constexpr int PF = kTilePF;
+    const int lane = threadIdx.x & 63;
+    const uint4* wp[CT];     // wave-uniform; the lane joins at the load
+#pragma unroll
+    for (int c = 0; c < CT; ++c) wp[c] = (const uint4*)(WP) + (int64_t)t[c] * nch * 64;
+    const char* ap = A + (lane & 15) * sa + 16 * (lane >> 4);
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int r = 0; r < MR; ++r) acc[c][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto rows = [&](int kc, bf16x8 (&a)[MR]) {
+#pragma unroll
+        for (int r = 0; r < MR; ++r) a[r] = *(const bf16x8*)(ap + 16 * r * sa + 64 * kc);
+    };
+    auto multiply = [&](const uint4 (&w)[CT], const bf16x8 (&a)[MR]) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int r = 0; r < MR; ++r)
+                acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[c]), a[r], acc[c][r], 0,
+                                                                   0, 0);
+    };
+    uint4 q[PF][CT];
+    bf16x8 a[2][MR];
+    auto fetch = [&](int kc, uint4 (&d)[CT]) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) d[c] = wp[c][64 * kc + lane];
+    };
+    // The scheduling barriers keep the loads where they are written: left alone, the
+    // compiler moves them next to their uses and every step waits for the L2.
+#pragma unroll
+    for (int d = 0; d < PF; ++d) fetch(d, q[d]);
+    rows(0, a[0]);
+    int kc = 0;
+    for (; kc + PF <= nch; kc += PF) {
+#pragma unroll
+        for (int d = 0; d < PF; ++d) {
+            rows(kc + d + 1, a[(d + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(q[d], a[d & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(kc + d + PF, q[d]);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < PF - 1; ++d)
+        if (kc + d < nch) {
+            rows(kc + d + 1, a[(d + 1) & 1]);
+            multiply(q[d], a[d & 1]);
+        }
+}
+
+// Every column of a layer for the workgroup's rows: store(col, row, bias, v) takes four
+// consecutive columns of one row and their biases.
+template <int MR, class Store>
+__device__ __forceinline__ void tile_layer(const char* A, int sa, const uint16_t* __restrict__ WP,
+                                           const float* __restrict__ bias, int ncols, int K, Store store) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tiles = (ncols + 15) >> 4, nch = (K + 31) >> 5;
+    auto run = [&](auto ctc, const int t0) {
+        constexpr int CT = decltype(ctc)::value;
+        f32x4 acc[CT][MR];
+        int t[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) t[c] = t0 + kTileWaves * c;
+        float bv[CT][4];
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bv[c][j] = bias[min(16 * t[c] + 4 * (lane >> 4) + j, ncols - 1)];
+        tile_product<MR, CT>(acc, A, sa, WP, t, nch);
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int r = 0; r < MR; ++r) store(16 * t[c] + 4 * (lane >> 4), 16 * r + (lane & 15), bv[c], acc[c][r]);
+    };
+    for (int t0 = wave; t0 < tiles; t0 += 2 * kTileWaves) {
+        if (t0 + kTileWaves < tiles) run(std::integral_constant<int, 2>(), t0);
+        else run(std::integral_constant<int, 1>(), t0);
+    }
+}
+
+// bf16(gelu(v + bias)) of four columns into the next layer's LDS rows (the columns of a
+// hidden layer are a multiple of 16).
+__device__ __forceinline__ void store_hidden(char* H, int sh, const float (&bias)[4], int col, int row, f32x4 v) {
+    float x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = v[j] + bias[j];
+    uint32_t h[4];
+    gelu_bf16(x, h);
+    *(uint2*)(H + row * sh + 2 * col) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+}
+
+// Row strides in bytes of an LDS tile of `ld` bf16 columns: 16 bytes more than the row,
+// so the 16 rows of a fragment start in distinct banks.
+__host__ __device__ inline int tile_stride(int ld) { return 2 * ld + 16; }
+
+}  // namespace labsdev

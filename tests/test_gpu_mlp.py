@@ -95,6 +95,37 @@ def test_forward_logits_128_tiles(lb, orc):
     assert err.max() <= 1e-2, err.max()
 
 
+@pytest.mark.parametrize("L,hidden", [(5, 64), (53, 192), (101, 256), (639, 256), (1023, 256)])
+@pytest.mark.parametrize("n", [1, 15, 17, 63, 65, 4097, 8193])
+def test_forward_row_tiles(lb, L, hidden, n):
+    """The one-workgroup forward pass at the edges of its row tiles (16 rows up to
+    4,096, 32 up to 8,192, then 64), against the separate products: the same network
+    widened to 320 hidden units whose weights are zero takes those, and appends only
+    exact zeros to every sum, so the logits are equal bit for bit.  The layout's pads
+    hold NaN."""
+    import torch
+    lay, P, _, _ = _params(lb, L, hidden, 57)
+    wide = lb.mlp_layout(L, 320)
+    Q = {key: np.zeros(s, np.float32) for key, s in
+         (("W1", (320, lay.d_in)), ("b1", 320), ("W2", (320, 320)), ("b2", 320),
+          ("W3", (lay.d_out, 320)), ("b3", lay.d_out))}
+    for key in Q:
+        Q[key][tuple(slice(0, d) for d in P[key].shape)] = P[key]
+    X = lb.mlp_features(L, _dev_i32(li.pack(li.random_skew(17 * L, n, L, 0))))
+    X[:, lay.d_in:] = float("nan")
+    out = []
+    for y, D in ((lay, P), (wide, Q)):
+        blob = lb.mlp_blob_from_dict(y, D)
+        W1 = blob[y.off_W1:y.off_W1 + y.hidden * y.ld_in].reshape(y.hidden, y.ld_in)
+        W1[:, y.d_in:] = np.nan
+        blob[y.off_W3 + y.d_out * y.hidden:y.off_W3 + y.ld_out * y.hidden] = np.nan
+        blob = torch.from_numpy(blob).cuda()
+        pb = torch.empty(y.n_params, dtype=torch.bfloat16, device="cuda")
+        lb.mlp_cast(y, blob, pb)
+        out.append(lb.mlp_forward(y, blob, pb, X)[:, :y.d_out].contiguous().view(torch.int32))
+    assert torch.equal(*out)
+
+
 @pytest.mark.parametrize("L,hidden,n", [(37, 64, 100), (101, 64, 257), (501, 256, 512), (501, 256, 4096)])
 def test_gradients(lb, orc, L, hidden, n):
     """Every gradient element against the oracle's, with a tolerance of its own:
