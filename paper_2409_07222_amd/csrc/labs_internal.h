@@ -93,6 +93,23 @@ __device__ __forceinline__ int packed_bit(const uint32_t* w, int i) {
     return (w[(i - 1) >> 5] >> (31 - ((i - 1) & 31))) & 1;
 }
 
+// C_d = (L-d) - 2 popcount(b XOR (b << d)), d >= 1, over the L-d overlapping bits of
+// the packed string b (zero words beyond its last).
+__device__ __forceinline__ int packed_corr(const uint32_t* pk, int L, int d) {
+    const int len = L - d, q = (d + 31) >> 5, sh = (32 - d) & 31;
+    const int full = len >> 5;                    // words with 32 overlapping bits
+    uint32_t pc = 0, hi = pk[q - 1];
+    for (int w = 0; w < full; ++w) {
+        const uint32_t lo = pk[w + q];
+        pc = bcnt_add(pk[w] ^ __builtin_amdgcn_alignbit(hi, lo, sh), pc);
+        hi = lo;
+    }
+    const int rem = len & 31;
+    if (rem)
+        pc = bcnt_add((pk[full] ^ __builtin_amdgcn_alignbit(hi, pk[full + q], sh)) & ~(0xFFFFFFFFu >> rem), pc);
+    return len - 2 * (int)pc;
+}
+
 // ---------------------------------------------------------------- launchers
 labs_status launch_energy(int32_t L, int64_t n, const uint32_t* seqs, int32_t* E, int32_t* C,
                           hipStream_t st);

@@ -22,6 +22,13 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
     return 0.5f * (1.0f + t) + 0.5f * x * (1.0f - t * t) * du;
 }
 
+// The feature of lag 2m, bf16(c / len), len = L - 2m odd, |c| <= len < 1024, from the
+// hardware reciprocal: a quotient other than 0 and +-1 (exact here too) is at least
+// 1 / (512 len) of itself away from every midpoint of two bf16 values (nine bits), and
+// the product errs by less than 2^-22.
+__device__ __forceinline__ float corr_scale(int L, int m) { return __builtin_amdgcn_rcpf((float)(L - 2 * m)); }
+__device__ __forceinline__ uint16_t corr_feature(int c, float scale) { return f2bf((float)c * scale); }
+
 // bf16(gelu_f(x)) of four values.  x (1 - 1 / (1 + e^{2u})) from the hardware exponential
 // and reciprocal lies within 1e-6 |x| of gelu_f's value (both are within 5e-7 |x| of the
 // true one: tanhf and the sum 1 + tanh err by a few 2^-24, the exponential by
