@@ -280,8 +280,9 @@ labs_status mlp_forward(const labs_mlp_layout& y, const float* P, const uint16_t
 // mlp_forward_ws bytes, then any number of passes while the weights stay.
 bool mlp_packs(const labs_mlp_layout& y);
 labs_status mlp_pack(const labs_mlp_layout& y, const uint16_t* Pb, void* ws, size_t wsb, hipStream_t st);
-labs_status mlp_forward_packed(const labs_mlp_layout& y, const float* P, const void* ws, int64_t n, const uint16_t* X,
-                               float* logits, hipStream_t st);
+// The features come from packed sequences and their C_{2m} (C[ldc * row + m - 1]).
+labs_status mlp_forward_state(const labs_mlp_layout& y, const float* P, const void* ws, int64_t n, const uint32_t* seq,
+                              const int16_t* C, int ldc, float* logits, hipStream_t st);
 size_t mlp_grads_ws(const labs_mlp_layout& y, int64_t n);
 labs_status mlp_grads(const labs_mlp_layout& y, const float* P, const uint16_t* Pb, int64_t n, const uint16_t* X,
                       const uint32_t* mask, const int32_t* labels, float* G, float* loss, void* ws, size_t wsb,

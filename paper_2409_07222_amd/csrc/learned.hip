@@ -2,35 +2,30 @@
 // form): every candidate is rescored with its exact integer energy change, and
 // every fallback_every-th step is the plain walker's full scan.
 //
-// One wavefront per walker and step.  The walker state lives in HBM between
-// steps (packed sequence, energy, tabu deadlines, tenure, best), so the network
-// can run as batched products between two step launches; the C_{2m} table is
-// rebuilt each step from the packed bits (L-2m overlapping bits, popcount of
-// their XOR), which costs less than storing and reloading it.
+// A full scan is a launch of the plain walker's logging kernel over one step (over
+// thousands of steps when every step is one).  The steps between are two launches each, the
+// network's pass over all walkers and k_lw_step; the walker state lives in HBM between
+// them: packed sequence, C_{2m} as 16-bit integers, energy, tabu deadlines, tenure, best.
 #include "labs_internal.h"
 
 #include <climits>
-#include <map>
-#include <mutex>
-#include <string>
 
 namespace labsdev {
 
 namespace {
 
 constexpr int kLwLmax = 639;
-constexpr int kLwWmax = 20;
-constexpr int kLwKmax = 319;
 constexpr int kLogSegment = 4096;   // steps a launch of the logging walk
-constexpr int kLwSlots = 5;   // ceil((kLwKmax + 1) / 64) free positions per lane
+constexpr int kTabuPad = 320;       // readable integers around the tabu deadlines
 
 struct LwArgs {
-    int32_t L, p, k, nf, W, MW, ld_in, ld_out;
-    int32_t top_m, fallback_every, mode, log_every, steps, n_log;
+    int32_t L, p, k, nf, W, MW, ld_out, ldc;
+    int32_t top_m, mode, log_every, steps, t;
     int64_t n, walker_begin;
     uint64_t prop_seed;
     int32_t e_max;
     uint32_t* seq;
+    int16_t* C;            // [n * ldc], C_{2m} at m - 1, zeros behind k
     int32_t* E;
     const int32_t* tenure;
     int32_t* halted;
@@ -38,7 +33,6 @@ struct LwArgs {
     int32_t* bestE;
     int32_t* bestT;
     uint32_t* bestSeq;
-    int32_t* tstep;
     int64_t* evals;
     int32_t* hit;
     // first-hit stamps (n_levels = 0: off); hitmask [n] holds each walker's stamped levels
@@ -47,7 +41,6 @@ struct LwArgs {
     unsigned long long* hit_ticks;
     uint32_t* hitmask;
     const float* logits;
-    uint16_t* X;
     int32_t* traj;
     int32_t* moves;
     int16_t* cands;
@@ -56,62 +49,6 @@ struct LwArgs {
     int32_t* log_label;
 };
 
-struct LwLds {
-    uint32_t pk[kLwWmax + 1];
-    int32_t C[kLwKmax + 1];       // C[m] = C_{2m}, m = 1..k
-    int32_t cand[kLwKmax + 2];    // candidate positions a
-    int8_t sv[kLwLmax + 1];       // sv[i-1] = s_i
-};
-
-// C_d = (L-d) - 2 popcount(b XOR (b << d)) over the L-d overlapping bits.
-__device__ __forceinline__ int corr(const uint32_t* pk, int W, int L, int d) {
-    const int len = L - d, q = d >> 5, sh = d & 31;
-    int pc = 0;
-    for (int w = 0; w * 32 < len; ++w) {
-        const uint32_t hi = pk[w + q];
-        const uint32_t lo = (w + q + 1 < W) ? pk[w + q + 1] : 0u;
-        const uint32_t sft = sh ? ((hi << sh) | (lo >> (32 - sh))) : hi;
-        uint32_t x = pk[w] ^ sft;
-        const int rem = len - w * 32;
-        if (rem < 32) x &= ~(0xFFFFFFFFu >> rem);
-        pc += __popc(x);
-    }
-    return len - 2 * pc;
-}
-
-// Change of C_d when the set {a, b} flips (b = a for the centre): a product
-// s_x s_{x+d} changes sign exactly when one of x, x+d lies in the set.
-__device__ __forceinline__ int dC(const int8_t* sv, int L, int a, int b, int d) {
-    int ua = 0;
-    const int i1 = a + d, i2 = a - d;
-    if (i1 <= L && i1 != b) ua += sv[i1 - 1];
-    if (i2 >= 1 && i2 != b) ua += sv[i2 - 1];
-    int r = sv[a - 1] * ua;
-    if (b != a) {
-        int ub = 0;
-        const int j1 = b + d, j2 = b - d;
-        if (j1 <= L && j1 != a) ub += sv[j1 - 1];
-        if (j2 >= 1 && j2 != a) ub += sv[j2 - 1];
-        r += sv[b - 1] * ub;
-    }
-    return -2 * r;
-}
-
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t w = __shfl_xor(v, o);
-        v = w > v ? w : v;
-    }
-    return v;
-}
-__device__ __forceinline__ int64_t wave_min_i64(int64_t v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        const int64_t w = __shfl_xor(v, o);
-        v = w < v ? w : v;
-    }
-    return v;
-}
-
 // Order-preserving map of an FP32 score to uint32 (-0 counts as +0).
 __device__ __forceinline__ uint32_t score_bits(float f) {
     uint32_t u = __float_as_uint(f);
@@ -119,154 +56,394 @@ __device__ __forceinline__ uint32_t score_bits(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__global__ __launch_bounds__(64) void k_lw_step(LwArgs A) {
-    __shared__ LwLds S;
-    const int lane = threadIdx.x;
-    const int64_t j = blockIdx.x;
-    const int L = A.L, k = A.k, p = A.p, nf = A.nf, W = A.W;
-    const int t = A.tstep[j] + 1;
-    const bool full = ((t - 1) % A.fallback_every) == 0;
-    const int64_t tb = j * nf;
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// A walker is a row of 16 lanes; lane patterns that exchange its halves, quarters, pairs.
+constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E, kSwap4 = 0x141, kSwap8 = 0x140;
+template <int CTRL>
+__device__ __forceinline__ int swapped(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double swapped(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)swapped<CTRL>((int)(uint32_t)u), hi = (uint32_t)swapped<CTRL>((int)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ int row_min(int v) {
+    v = min(v, swapped<kSwap1>(v));
+    v = min(v, swapped<kSwap2>(v));
+    v = min(v, swapped<kSwap4>(v));
+    return min(v, swapped<kSwap8>(v));
+}
+
+// A candidate's key: a double of exponent 0 whose mantissa is the 32-bit score and, below
+// it, 2^20 - 1 - position, so one FP64 minimum or maximum orders (score, lower position
+// first) exactly; 0 where there is none.
+__device__ __forceinline__ double make_key(uint32_t score, int pos) {
+    return __builtin_bit_cast(double, (uint64_t)(0x3FF00000u | (score >> 12)) << 32 |
+                                          ((score << 20) | (uint32_t)(0xFFFFF - pos)));
+}
+__device__ __forceinline__ int key_pos(double key) {
+    return 0xFFFFF - (int)((uint32_t)__builtin_bit_cast(uint64_t, key) & 0xFFFFF);
+}
+__device__ __forceinline__ double kmax(double a, double b) { return __builtin_fmax(a, b); }
+__device__ __forceinline__ void order2(double& a, double& b) {   // a >= b
+    const double hi = __builtin_fmax(a, b), lo = __builtin_fmin(a, b);
+    a = hi;
+    b = lo;
+}
+// Sorts a bitonic list, largest first.
+template <int M>
+__device__ __forceinline__ void bitonic(double (&v)[M]) {
+#pragma unroll
+    for (int d = M / 2; d > 0; d /= 2)
+#pragma unroll
+        for (int i = 0; i < M; ++i)
+            if (!(i & d)) order2(v[i], v[i + d]);
+}
+// The M largest of this lane's list and its partner's, sorted, in both lanes.
+template <int CTRL, int M>
+__device__ __forceinline__ void merge_lanes(double (&v)[M]) {
+    double o[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) o[i] = swapped<CTRL>(v[M - 1 - i]);
+#pragma unroll
+    for (int i = 0; i < M; ++i) v[i] = kmax(v[i], o[i]);
+    bitonic(v);
+}
+
+// LDS of one walker: class rows (class 0: odd positions, 1: even; index n = (x - 1) >> 1)
+// as bytes +-1, zeros around them, and the bytes of C of four lags a group, {low, the
+// bytes above: (C + 128) >> 8}.
+template <int NQ>
+struct LwLds {
+    static constexpr int PAD = 24, ST = 64 * NQ + 2 * PAD;
+    int8_t x[2][ST] __attribute__((aligned(16)));
+    uint2 ct[16 * NQ] __attribute__((aligned(16)));
+    int32_t cand[64] __attribute__((aligned(16)));
+};
+
+// Four bits 6, 4, 2, 0 to the lowest bits of four bytes.
+__device__ __forceinline__ uint32_t spread4(uint32_t t) {
+    return ((t | (t << 10) | (t << 20) | (t << 30)) >> 6) & 0x01010101u;
+}
+
+// One narrow step: the top_m admissible positions by score, their exact dE, the move.
+// NQ: groups of 64 lags or positions, M: length of the candidate list a lane keeps (64:
+// the candidates are taken one at a time).  Bound by issue, so a walker is 16 lanes and
+// every part is spread over them without idle ones: keys (four positions a lane and
+// group), a merge of sorted lists instead of top_m reductions, and dE of a candidate by
+// 16/M lanes, four lags a dot product:
+//   dC_{2m} = -4 s_a (x[n+m] + x[n-m]) for a flipped pair (x[n+m] = s_b left out; at the
+//   centre -2 s_a), by the symmetry of the pair, so
+//   dE = 16 (k - 1 - cl) + 32 (sum_m x[n+m] x[n-m]) - 8 s_a sum_m C_{2m} (x[n+m] + x[n-m])
+//   with the partner's terms taken out, and at the centre 16 n - 4 s_a sum_m (same).
+// A wave a walker that rebuilt C, read the network's features' sources element by element
+// and wrote the features took 82 us a step of 16,384 walkers at L = 501, top 8; this takes
+// 17.6.
+template <int NQ, int M>
+__global__ __launch_bounds__(256) void k_lw_step(LwArgs A) {
+    typedef LwLds<NQ> T;
+    typedef short v2s __attribute__((ext_vector_type(2)));
+    struct __attribute__((packed, aligned(4))) int4u { int v[4]; };
+    constexpr int PER = M == 8 ? 8 : 16, NH = 16 / PER;
+    __shared__ T SS[16];
+    T& S = SS[threadIdx.x >> 4];
+    const int l = threadIdx.x & 15;
+    const int64_t j = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int L = A.L, k = A.k, p = A.p, W = A.W, t = A.t;
+    if (j >= A.n) return;                        // whole rows leave; rows do not meet again
     const int64_t ti = j * A.steps + (t - 1);
+    const int64_t tb = j * A.nf - p;
 
     if (A.halted[j]) {
-        if (lane == 0) {
+        if (l == 0) {
             if (A.traj) A.traj[ti] = -1;
             if (A.moves) A.moves[ti] = -1;
-            A.tstep[j] = t;
         }
         if (A.cands)
-            for (int i = lane; i < A.top_m; i += 64) A.cands[ti * A.top_m + i] = -1;
+            for (int i = l; i < A.top_m; i += 16) A.cands[ti * A.top_m + i] = -1;
         return;
     }
 
-    if (lane < W) S.pk[lane] = A.seq[j * W + lane];
-    if (lane == 0) S.pk[W] = 0;
-    __syncthreads();
-    for (int i = lane; i < L; i += 64) S.sv[i] = ((S.pk[i >> 5] >> (31 - (i & 31))) & 1) ? 1 : -1;
-    for (int m = 1 + lane; m <= k; m += 64) S.C[m] = corr(S.pk, W, L, 2 * m);
+    const int E0 = A.E[j], bE0 = A.bestE[j], tenure = A.tenure[j];
+    uint32_t word[2];
+    word[0] = l < W ? A.seq[j * W + l] : 0;
+    word[1] = NQ > 4 && l + 16 < W ? A.seq[j * W + l + 16] : 0;
+    v2s c01[NQ], c23[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const uint2 v = *(const uint2*)(A.C + j * A.ldc + 4 * (l + 16 * q));
+        c01[q] = __builtin_bit_cast(v2s, v.x);
+        c23[q] = __builtin_bit_cast(v2s, v.y);
+    }
 
-    // ---- candidates
+    // ---- keys of the admissible positions (position a - 1 = 4 (l + 16 q) + r)
+    double key[4 * NQ];
+    uint32_t adm = 0;                             // bit 4 q + r
+    const uint64_t rkey = A.mode == LABS_PROPOSE_RANDOM ? walker_key(A.prop_seed, L, A.walker_begin + j) : 0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int pos0 = 4 * (l + 16 * q);
+        const int4u until = *(const int4u*)(A.tabu + tb + pos0);
+        uint32_t sc[4] = {0, 0, 0, 0};
+        if (A.mode == LABS_PROPOSE_MLP) {
+            if (64 * q < A.ld_out) {
+                const float4 z = *(const float4*)(A.logits + j * A.ld_out + pos0);
+                sc[0] = score_bits(z.x);
+                sc[1] = score_bits(z.y);
+                sc[2] = score_bits(z.z);
+                sc[3] = score_bits(z.w);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                sc[r] = (uint32_t)(sm64_at(rkey, (uint64_t)(t - 1) * (uint64_t)(k + 1) + (uint64_t)(pos0 + r)) >> 32);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool ok = pos0 + r >= p && pos0 + r <= k && until.v[r] < t;
+            adm |= (ok ? 1u : 0u) << (4 * q + r);
+            key[4 * q + r] = ok ? make_key(sc[r], pos0 + r) : 0.0;
+        }
+    }
+
+    // ---- class rows and the bytes of C
+#pragma unroll
+    for (int h = 0; h < (NQ > 4 ? 2 : 1); ++h) {
+        const int w = l + 16 * h;
+        if (w < W) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                uint32_t d[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t z = spread4((~word[h] >> (24 - 8 * q + 1 - c)) & 0x55u);   // 1 where x = -1
+                    d[q] = 0x01010101u + (z << 8) - (z << 1);
+                }
+                *(uint2*)(S.x[c] + T::PAD + 16 * w) = make_uint2(d[0], d[1]);
+                *(uint2*)(S.x[c] + T::PAD + 16 * w + 8) = make_uint2(d[2], d[3]);
+            }
+        }
+    }
+    lds_order();
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        // zeros ahead, behind the last element (k + 1 of class 0, k of class 1), behind the words
+        const int size = k + 1 - c;
+        if (size + l < 16 * W) S.x[c][T::PAD + size + l] = 0;
+        if (l < 6) *(uint32_t*)(S.x[c] + 4 * l) = 0;
+        if (l < 6) *(uint32_t*)(S.x[c] + T::PAD + 16 * W + 4 * l) = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const v2s bias = {128, 128};
+        uint2 v;
+        v.x = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, c23[q]), __builtin_bit_cast(uint32_t, c01[q]),
+                                    0x06040200u);
+        v.y = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, (v2s)(c23[q] + bias)),
+                                    __builtin_bit_cast(uint32_t, (v2s)(c01[q] + bias)), 0x07050301u);
+        S.ct[l + 16 * q] = v;
+    }
+
+    // ---- the candidates
     int ncand = 0;
-    if (full) {
-        for (int f0 = 0; f0 < nf; f0 += 64) {
-            const int f = f0 + lane;
-            const bool ok = f < nf && A.tabu[tb + f] < t;
-            const uint64_t bal = __ballot(ok);
-            if (ok) S.cand[ncand + __popcll(bal & ((1ull << lane) - 1ull))] = p + 1 + f;
-            ncand += __popcll(bal);
+    if constexpr (M <= 16) {
+        double v[M];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            double* s = key + 4 * q;
+            order2(s[0], s[1]);
+            order2(s[2], s[3]);
+            order2(s[0], s[2]);
+            order2(s[1], s[3]);
+            order2(s[1], s[2]);
+            if (q == 0) {
+#pragma unroll
+                for (int i = 0; i < M; ++i) v[i] = i < 4 ? s[i] : 0.0;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[M - 4 + i] = kmax(v[M - 4 + i], s[3 - i]);
+                bitonic(v);
+            }
+        }
+        merge_lanes<kSwap1>(v);
+        merge_lanes<kSwap2>(v);
+        merge_lanes<kSwap4>(v);
+        merge_lanes<kSwap8>(v);
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            ncand += v[i] != 0.0 && i < A.top_m ? 1 : 0;
+            if (l == 0) S.cand[i] = key_pos(v[i]) + 1;
         }
     } else {
-        uint64_t key[kLwSlots];
-        uint64_t rkey = 0;
-        if (A.mode == LABS_PROPOSE_RANDOM) rkey = walker_key(A.prop_seed, L, A.walker_begin + j);
-        for (int r = 0; r < kLwSlots; ++r) {
-            const int f = lane + 64 * r;
-            key[r] = 0;
-            if (f < nf && A.tabu[tb + f] < t) {
-                const int a = p + 1 + f;
-                uint32_t sc;
-                if (A.mode == LABS_PROPOSE_MLP)
-                    sc = score_bits(A.logits[j * A.ld_out + (a - 1)]);
-                else
-                    sc = (uint32_t)(sm64_at(rkey, (uint64_t)(t - 1) * (uint64_t)(k + 1) + (uint64_t)(a - 1)) >> 32);
-                key[r] = ((uint64_t)sc << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)f);
-            }
-        }
-        for (int c = 0; c < A.top_m; ++c) {
-            uint64_t best = 0;
-            for (int r = 0; r < kLwSlots; ++r) best = key[r] > best ? key[r] : best;
-            best = wave_max_u64(best);
-            if (best == 0) break;
-            for (int r = 0; r < kLwSlots; ++r)
-                if (key[r] == best) key[r] = 0;
-            if (lane == 0) S.cand[c] = p + 1 + (int)(0xFFFFFFFFu - (uint32_t)best);
-            ++ncand;
+        for (; ncand < A.top_m; ++ncand) {
+            double best = key[0];
+#pragma unroll
+            for (int i = 1; i < 4 * NQ; ++i) best = kmax(best, key[i]);
+            best = kmax(best, swapped<kSwap1>(best));
+            best = kmax(best, swapped<kSwap2>(best));
+            best = kmax(best, swapped<kSwap4>(best));
+            best = kmax(best, swapped<kSwap8>(best));
+            if (best == 0.0) break;
+#pragma unroll
+            for (int i = 0; i < 4 * NQ; ++i)
+                if (key[i] == best) key[i] = 0.0;
+            if (l == 0) S.cand[ncand] = key_pos(best) + 1;
         }
     }
-    __syncthreads();
-
-    // ---- exact dE of every candidate: lanes split over (candidate, lag group)
-    int G = 1;
-    if (ncand < 64) {
-        int p2 = 1;
-        while (p2 < ncand) p2 <<= 1;
-        G = 64 / p2;
-    }
-    const int per = 64 / G;
-    int64_t bestkey = LLONG_MAX;
-    for (int c0 = 0; c0 < ncand; c0 += per) {
-        const int c = c0 + lane / G, g = lane % G;
-        int acc = 0, a = 0;
-        if (c < ncand) {
-            a = S.cand[c];
-            const int b = L + 1 - a;
-            for (int m = 1 + g; m <= k; m += G) {
-                const int d = dC(S.sv, L, a, b, 2 * m);
-                acc += d * (2 * S.C[m] + d);
-            }
-        }
-        for (int o = G >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-        if (c < ncand && g == 0) {
-            const int64_t key = (int64_t)acc * 4294967296LL + (int64_t)a;
-            bestkey = key < bestkey ? key : bestkey;
-        }
-    }
-    bestkey = wave_min_i64(bestkey);
+    lds_order();
 
     if (ncand == 0) {   // no admissible move: the walk halts here
-        if (lane == 0) {
+        if (l == 0) {
             A.halted[j] = t;
             if (A.traj) A.traj[ti] = -1;
             if (A.moves) A.moves[ti] = -1;
-            A.tstep[j] = t;
         }
         if (A.cands)
-            for (int i = lane; i < A.top_m; i += 64) A.cands[ti * A.top_m + i] = -1;
+            for (int i = l; i < A.top_m; i += 16) A.cands[ti * A.top_m + i] = -1;
         return;
     }
-    const int dE = (int)(bestkey >> 32);
-    const int a = (int)(bestkey & 0xFFFFFFFFLL);
-    const int b = L + 1 - a;
-    const int E0 = A.E[j], bE0 = A.bestE[j], newE = E0 + dE;
+
+    // ---- exact dE of every candidate, blocks of 16 lags
+    int dE = INT_MAX, a = INT_MAX;
+    for (int c0 = 0; c0 < ncand; c0 += PER) {
+        const int c = c0 + (l % PER);
+        const int ca = S.cand[c < ncand ? c : 0], x1 = ca - 1, cl = x1 & 1, n = x1 >> 1;
+        const int8_t* const x = S.x[cl] + T::PAD;
+        const int size = k + 1 - cl;
+        const int8_t* const pf = x + ((n + 1) & ~3);
+        const int8_t* const pb = x + ((n - 4) & ~3);
+        const uint32_t sf = 0x03020100u + 0x01010101u * (uint32_t)((n + 1) & 3);
+        const uint32_t sb = 0x00010203u + 0x01010101u * (uint32_t)(n & 3);
+        int lo = 0, hi = 0, y = 0;
+        for (int b0 = 16 * (l / PER); b0 < k; b0 += 16 * NH) {
+            if (n + 1 + b0 >= size) break;        // both ends of every pair are outside
+            const uint4 g0 = *(const uint4*)&S.ct[b0 / 4], g1 = *(const uint4*)&S.ct[b0 / 4 + 2];
+            const uint32_t cl4[4] = {g0.x, g0.z, g1.x, g1.z}, ch4[4] = {g0.y, g0.w, g1.y, g1.w};
+            uint32_t f[4], w[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) w[i] = *(const uint32_t*)(pf + b0 + 4 * i);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                f[i] = __builtin_amdgcn_perm(w[i + 1], w[i], sf);
+                lo = __builtin_amdgcn_sdot4((int)f[i], (int)cl4[i], lo, false);
+                hi = __builtin_amdgcn_sdot4((int)f[i], (int)ch4[i], hi, false);
+            }
+            if (b0 < n) {
+#pragma unroll
+                for (int i = 0; i < 5; ++i) w[i] = *(const uint32_t*)(pb - b0 + 4 - 4 * i);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t g = __builtin_amdgcn_perm(w[i], w[i + 1], sb);
+                    lo = __builtin_amdgcn_sdot4((int)g, (int)cl4[i], lo, false);
+                    hi = __builtin_amdgcn_sdot4((int)g, (int)ch4[i], hi, false);
+                    y = __builtin_amdgcn_sdot4((int)g, (int)f[i], y, false);
+                }
+            }
+        }
+        int s = lo + 256 * hi;
+        if constexpr (NH > 1) {
+            s += swapped<0x128>(s);               // row_ror:8
+            y += swapped<0x128>(y);
+        }
+        const int sa = x[n], nb = k - n - cl, mp = nb - n;
+        int d;
+        if (mp == 0) {
+            d = 16 * n - 4 * sa * s;
+        } else {
+            const int xb = x[nb], xm = x[n - mp > -1 ? n - mp : -1];
+            const uint2 g = S.ct[(mp - 1) >> 2];
+            const int sh = 8 * ((mp - 1) & 3);
+            const int cm = (int8_t)(g.x >> sh) + 256 * (int8_t)(g.y >> sh);
+            d = 16 * (k - 1 - cl) + 32 * (y - xb * xm) - 8 * sa * (s - cm * xb);
+        }
+        if (c < ncand && (d < dE || (d == dE && ca < a))) {
+            dE = d;
+            a = ca;
+        }
+    }
+    const int dmin = row_min(dE);
+    a = row_min(dE == dmin ? a : INT_MAX);
+    const int newE = E0 + dmin;
+    const int x1 = a - 1, cl = x1 & 1, n = x1 >> 1, nb = k - n - cl;
+    const bool cen = n == nb;
 
     // ---- training log: the state before the move
     if (A.log_every > 0 && t % A.log_every == 0) {
         const int64_t r = (int64_t)(t / A.log_every - 1) * A.n + j;   // step-major records
-        if (lane < W) A.log_seqs[r * W + lane] = S.pk[lane];
-        for (int w = lane; w < A.MW; w += 64) {
-            uint32_t bits = 0;
-            for (int q = 0; q < 32; ++q) {
-                const int pos = 32 * w + q + 1;
-                if (pos > p && pos <= k + 1 && A.tabu[tb + pos - p - 1] < t) bits |= 1u << q;
-            }
-            A.log_mask[r * A.MW + w] = bits;
+        if (l < W) A.log_seqs[r * W + l] = word[0];
+        if (NQ > 4 && l + 16 < W) A.log_seqs[r * W + l + 16] = word[1];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            int bits = (int)(((adm >> (4 * q)) & 15u) << (4 * (l & 7)));   // 8 lanes a word
+            bits |= swapped<kSwap1>(bits);
+            bits |= swapped<kSwap2>(bits);
+            bits |= swapped<kSwap4>(bits);
+            const int w = 2 * q + (l >> 3);
+            if ((l & 7) == 0 && w < A.MW) A.log_mask[r * A.MW + w] = (uint32_t)bits;
         }
-        if (lane == 0) A.log_label[r] = a - 1;
+        if (l == 0) A.log_label[r] = a - 1;
     }
     if (A.cands)
-        for (int i = lane; i < A.top_m; i += 64) A.cands[ti * A.top_m + i] = (!full && i < ncand) ? (int16_t)S.cand[i] : (int16_t)-1;
-    __syncthreads();
+        for (int i = l; i < A.top_m; i += 16)
+            A.cands[ti * A.top_m + i] = i < ncand ? (int16_t)S.cand[i] : (int16_t)-1;
 
-    // ---- apply
-    if (lane == 0) {
-        S.pk[(a - 1) >> 5] ^= 1u << (31 - ((a - 1) & 31));
-        if (b != a) S.pk[(b - 1) >> 5] ^= 1u << (31 - ((b - 1) & 31));
+    // ---- apply: C with the partner's byte out of its row
+    int8_t* const x = S.x[cl] + T::PAD;
+    const int sa = x[n];
+    lds_order();
+    if (l == 0 && !cen) x[nb] = 0;
+    lds_order();
+    {
+        const uint32_t sf = 0x03020100u + 0x01010101u * (uint32_t)((n + 1) & 3);
+        const uint32_t sb = 0x00010203u + 0x01010101u * (uint32_t)(n & 3);
+        const short mul = (short)(cen ? -2 * sa : -4 * sa);
+        const v2s mul2 = {mul, mul};
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int m0 = 4 * (l + 16 * q);
+            const int of = min(((n + 1) & ~3) + m0, 16 * W + 16), ob = max(((n - 4) & ~3) - m0, -8);
+            const uint32_t f = __builtin_amdgcn_perm(*(const uint32_t*)(x + of + 4), *(const uint32_t*)(x + of), sf);
+            const uint32_t b = __builtin_amdgcn_perm(*(const uint32_t*)(x + ob + 4), *(const uint32_t*)(x + ob), sb);
+            const v2s u01 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(f, f, 0x010C000Cu)) +
+                            __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b, b, 0x010C000Cu));
+            const v2s u23 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(f, f, 0x030C020Cu)) +
+                            __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b, b, 0x030C020Cu));
+            c01[q] += (u01 >> 8) * mul2;
+            c23[q] += (u23 >> 8) * mul2;
+            *(uint2*)(A.C + j * A.ldc + m0) =
+                make_uint2(__builtin_bit_cast(uint32_t, c01[q]), __builtin_bit_cast(uint32_t, c23[q]));
+        }
+    }
+    const int x2 = L - a;                         // the partner's place in the string
+#pragma unroll
+    for (int h = 0; h < (NQ > 4 ? 2 : 1); ++h) {
+        const int w = l + 16 * h;
+        uint32_t v = word[h];
+        if (w == x1 >> 5) v ^= 1u << (31 - (x1 & 31));
+        if (w == x2 >> 5 && !cen) v ^= 1u << (31 - (x2 & 31));
+        if (w < W) {
+            if (v != word[h]) A.seq[j * W + w] = v;
+            if (newE < bE0) A.bestSeq[j * W + w] = v;
+        }
+    }
+    if (l == 0) {
         A.E[j] = newE;
-        A.tabu[tb + (a - p - 1)] = t + A.tenure[j];
+        A.tabu[tb + x1] = t + tenure;
         if (A.traj) A.traj[ti] = newE;
         if (A.moves) A.moves[ti] = a;
         A.evals[j] += ncand;
-        A.tstep[j] = t;
         if (A.e_max >= 0 && newE <= A.e_max && A.hit[j] < 0) A.hit[j] = t;
         if (A.n_levels > 0) {
             const unsigned long long now = __builtin_amdgcn_s_memrealtime();
             uint32_t hm = A.hitmask[j];
             const uint32_t hm0 = hm;
-            for (int l = 0; l < A.n_levels; ++l)
-                if (!((hm >> l) & 1u) && newE <= A.level_E[l]) {
-                    atomicMin(&A.hit_ticks[l], now);
-                    hm |= 1u << l;
+            for (int q = 0; q < A.n_levels; ++q)
+                if (!((hm >> q) & 1u) && newE <= A.level_E[q]) {
+                    atomicMin(&A.hit_ticks[q], now);
+                    hm |= 1u << q;
                 }
             if (hm != hm0) A.hitmask[j] = hm;
         }
@@ -275,35 +452,46 @@ __global__ __launch_bounds__(64) void k_lw_step(LwArgs A) {
             A.bestT[j] = t;
         }
     }
-    __syncthreads();
-    if (lane < W) {
-        A.seq[j * W + lane] = S.pk[lane];
-        if (newE < bE0) A.bestSeq[j * W + lane] = S.pk[lane];
-    }
-
-    // ---- features of the new state for the next step's network pass
-    if (A.X && (t % A.fallback_every) != 0 && t < A.steps) {
-        uint16_t* x = A.X + j * A.ld_in;
-        for (int i = lane; i < A.ld_in; i += 64) {
-            uint16_t v = 0;
-            if (i < L) {
-                int s = S.sv[i];
-                if (i + 1 == a || i + 1 == b) s = -s;
-                v = s > 0 ? (uint16_t)0x3F80 : (uint16_t)0xBF80;
-            } else if (i < L + k) {
-                const int m = i - L + 1, d = 2 * m;
-                const int c = S.C[m] + dC(S.sv, L, a, b, d);
-                v = f2bf((float)c / (float)(L - d));
-            }
-            x[i] = v;
-        }
-    }
 }
 
-__global__ void k_lw_init(int64_t n, int32_t* tstep, int64_t* evals, int32_t* hit, uint32_t* hitmask) {
+// After a full scan: C of the walker's sequence, and no candidates logged for the step.
+__global__ __launch_bounds__(256) void k_lw_corr(LwArgs A) {
+    __shared__ uint32_t sw[4][24];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t j = (int64_t)blockIdx.x * 4 + wv;
+    if (lane < 24) sw[wv][lane] = j < A.n && lane < A.W ? A.seq[j * A.W + lane] : 0u;
+    __syncthreads();
+    if (j >= A.n) return;
+    for (int i = lane; i < A.ldc; i += 64)
+        A.C[j * A.ldc + i] = i < A.k ? (int16_t)packed_corr(sw[wv], A.L, 2 * i + 2) : (int16_t)0;
+    if (A.cands)
+        for (int i = lane; i < A.top_m; i += 64) A.cands[(j * A.steps + A.t - 1) * A.top_m + i] = -1;
+}
+
+// 64-lag groups of the step's kernel: 2, 4 or 5.
+int lw_groups(int k) { return k < 128 ? 2 : k < 256 ? 4 : 5; }
+
+template <int NQ>
+void launch_lw_step_nq(const LwArgs& A, hipStream_t st) {
+    const dim3 grid((unsigned)((A.n + 15) / 16)), block(256);
+    if (A.top_m <= 8) hipLaunchKernelGGL((k_lw_step<NQ, 8>), grid, block, 0, st, A);
+    else if (A.top_m <= 16) hipLaunchKernelGGL((k_lw_step<NQ, 16>), grid, block, 0, st, A);
+    else hipLaunchKernelGGL((k_lw_step<NQ, 64>), grid, block, 0, st, A);
+}
+
+labs_status launch_lw_step(const LwArgs& A, hipStream_t st) {
+    switch (A.ldc) {
+        case 128: launch_lw_step_nq<2>(A, st); break;
+        case 256: launch_lw_step_nq<4>(A, st); break;
+        default: launch_lw_step_nq<5>(A, st); break;
+    }
+    LABS_LAUNCHED("k_lw_step");
+    return LABS_OK;
+}
+
+__global__ void k_lw_init(int64_t n, int64_t* evals, int32_t* hit, uint32_t* hitmask) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) {
-        tstep[i] = 0;
         evals[i] = 0;
         hit[i] = -1;
         hitmask[i] = 0;
@@ -347,6 +535,7 @@ struct LwBuffers {
     LwArgs la;
     void* fwd_ws;
     size_t fwd_bytes;
+    uint16_t* X;    // features, for a network that does not pack
     size_t bytes;   // workspace used
     bool ok;
 };
@@ -366,7 +555,8 @@ LwBuffers carve_lw(const labs_step1_cfg& c, const labs_proposer& pr, const labs_
     w.E = cv.take<int32_t>(n);
     w.tenure = cv.take<int32_t>(n);
     w.halted = cv.take<int32_t>(n);
-    w.tabu = cv.take<int32_t>((size_t)n * nf);
+    w.tabu = cv.take<int32_t>((size_t)n * nf + 2 * kTabuPad);
+    if (w.tabu) w.tabu += kTabuPad;
     w.bestE = cv.take<int32_t>(n);
     w.bestT = cv.take<int32_t>(n);
     w.bestSeq = cv.take<uint32_t>((size_t)n * W);
@@ -374,20 +564,19 @@ LwBuffers carve_lw(const labs_step1_cfg& c, const labs_proposer& pr, const labs_
     w.e_max = c.e_max;
     LwArgs& a = B.la;
     a.L = L; a.p = c.p; a.k = k; a.nf = nf; a.W = W; a.MW = (k + 1 + 31) / 32;
-    a.ld_in = lay ? lay->ld_in : 0;
+    a.ldc = 64 * lw_groups(k);
     a.ld_out = lay ? lay->ld_out : 0;
-    a.top_m = pr.top_m; a.fallback_every = pr.fallback_every; a.mode = pr.mode;
+    a.top_m = pr.top_m; a.mode = pr.mode;
     a.log_every = pr.log_every; a.steps = c.steps;
-    a.n_log = pr.log_every > 0 ? c.steps / pr.log_every : 0;
     a.n = n; a.walker_begin = c.walker_begin; a.prop_seed = pr.seed; a.e_max = c.e_max;
     a.seq = w.seq; a.E = w.E; a.tenure = w.tenure; a.halted = w.halted; a.tabu = w.tabu;
     a.bestE = w.bestE; a.bestT = w.bestT; a.bestSeq = w.bestSeq;
-    a.tstep = cv.take<int32_t>(n);
+    a.C = cv.take<int16_t>((size_t)n * a.ldc);
     a.evals = cv.take<int64_t>(n);
     a.hit = cv.take<int32_t>(n);
     a.hitmask = cv.take<uint32_t>(n);
     if (lay) {
-        a.X = cv.take<uint16_t>((size_t)n * lay->ld_in);
+        B.X = mlp_packs(*lay) ? nullptr : cv.take<uint16_t>((size_t)n * lay->ld_in);
         a.logits = cv.take<float>((size_t)n * lay->ld_out);
         B.fwd_bytes = mlp_forward_ws(*lay, n);
         B.fwd_ws = cv.take<char>(B.fwd_bytes);
@@ -396,17 +585,6 @@ LwBuffers carve_lw(const labs_step1_cfg& c, const labs_proposer& pr, const labs_
     B.ok = cv.ok() && ws != nullptr;
     return B;
 }
-
-hipStream_t capture_stream_lw() {
-    static hipStream_t cs = nullptr;
-    if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) cs = nullptr;
-    return cs;
-}
-
-// Executable graphs of one period of steps, keyed by everything their launches
-// capture (kernel arguments and network pointers); kept until the process ends.
-std::mutex g_lw_mu;
-std::map<std::string, hipGraphExec_t> g_lw_graphs;
 
 }  // namespace
 
@@ -439,110 +617,59 @@ labs_status learned_walk(const labs_step1_cfg& c, const labs_proposer& pr, const
         for (int l = 0; l < LABS_MAX_LEVELS; ++l) A.level_E[l] = B.wa.level_E[l];
         A.hit_ticks = B.wa.hit_ticks;
     }
-    if (!mlp) {
-        A.X = nullptr;
-        A.logits = nullptr;
-    }
     const int64_t n = A.n;
     labs_status s = launch_walker_init(B.wa, st);
     if (s) return s;
-    hipLaunchKernelGGL(k_lw_init, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, A.tstep, A.evals, A.hit,
-                       A.hitmask);
+    hipLaunchKernelGGL(k_lw_init, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, A.evals, A.hit, A.hitmask);
     LABS_LAUNCHED("k_lw_init");
 
     const int64_t tot = n * A.W > n ? n * A.W : n;
     const int F = pr.fallback_every;
-    if (F == 1) {
-        // Every step a full exact scan: the plain walker's kernel, whose matrix-core scan
-        // costs a hundredth of a step here (16,384 walkers at L = 501, a record every 7
-        // steps: 705 -> 5.6 us a step).
-        WalkArgs& w = B.wa;
-        w.traj = o.traj_E;
-        w.moves = o.moves;
-        w.hit = A.hit;
-        w.evals = A.evals;
-        w.log_every = A.log_every;
-        w.MW = A.MW;
-        w.log_seqs = A.log_seqs;
-        w.log_mask = A.log_mask;
-        w.log_label = A.log_label;
-        for (int t0 = 0; t0 < c.steps; t0 += kLogSegment) {
-            w.t0 = t0;
-            w.t1 = t0 + kLogSegment < c.steps ? t0 + kLogSegment : c.steps;
-            if ((s = launch_walk_log(w, st))) return s;
-        }
-        if (o.cands) {
-            const int64_t cn = n * c.steps * A.top_m;
-            hipLaunchKernelGGL(k_fill_i16, dim3((unsigned)(cn / 256 + 1 < 65536 ? cn / 256 + 1 : 65536)), dim3(256), 0,
-                               st, cn, o.cands, (int16_t)-1);
-            LABS_LAUNCHED("k_fill_i16");
-        }
-        hipLaunchKernelGGL(k_lw_outputs, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, A, o.final_seqs,
-                           o.final_E, o.best_seqs, o.best_E, o.best_step, o.hit_step);
-        LABS_LAUNCHED("k_lw_outputs");
-        hipLaunchKernelGGL(k_sum_i64, dim3(1), dim3(256), 0, st, n, A.evals, o.flip_evals);
-        LABS_LAUNCHED("k_sum_i64");
-        return LABS_OK;
-    }
-
+    // Full scans by the plain walker's kernel, whose matrix-core scan costs a hundredth of
+    // one by candidates (16,384 walkers at L = 501, a record every 7 steps: 705 -> 5.6 us a
+    // step, 92 with its setup in a launch of its own).
+    WalkArgs& w = B.wa;
+    w.traj = o.traj_E;
+    w.moves = o.moves;
+    w.hit = A.hit;
+    w.evals = A.evals;
+    w.log_every = A.log_every;
+    w.MW = A.MW;
+    w.log_seqs = A.log_seqs;
+    w.log_mask = A.log_mask;
+    w.log_label = A.log_label;
     const bool packed = mlp && mlp_packs(lay);
-    if (packed && (s = mlp_pack(lay, pr.params_bf16, B.fwd_ws, B.fwd_bytes, st))) return s;
-
-    // One launch sequence per step; steps t with (t-1) mod F == 0 need no network pass.
-    auto enqueue_step = [&](int t, hipStream_t q) -> labs_status {
-        if (mlp && ((t - 1) % F) != 0) {
-            labs_status r = packed ? mlp_forward_packed(lay, pr.params, B.fwd_ws, n, A.X, const_cast<float*>(A.logits), q)
-                                   : mlp_forward(lay, pr.params, pr.params_bf16, n, A.X, const_cast<float*>(A.logits),
-                                                 B.fwd_ws, B.fwd_bytes, q);
-            if (r) return r;
-        }
-        hipLaunchKernelGGL(k_lw_step, dim3((unsigned)n), dim3(64), 0, q, A);
-        LABS_LAUNCHED("k_lw_step");
-        return LABS_OK;
-    };
-    // The launch pattern repeats with period F (network mode) or 1; a block of
-    // `period` steps is recorded once into a graph and replayed.
-    const int period = mlp ? F : 64;
-    const int reps = c.steps / period;
-    int t = 1;
-    if (reps >= 2) {
-        std::string key((const char*)&A, sizeof(A));
-        key.append((const char*)&pr, sizeof(pr));
-        key.append((const char*)&B.fwd_ws, sizeof(B.fwd_ws));
-        key.append((const char*)&period, sizeof(period));
-        std::lock_guard<std::mutex> g(g_lw_mu);
-        hipGraphExec_t exec = nullptr;
-        auto it = g_lw_graphs.find(key);
-        if (it != g_lw_graphs.end()) {
-            exec = it->second;
-        } else {
-            hipStream_t cs = capture_stream_lw();
-            if (!cs) return invalid("cannot create the graph capture stream");
-            LABS_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-            labs_status r = LABS_OK;
-            for (int q = 1; q <= period && r == LABS_OK; ++q) r = enqueue_step(q, cs);
-            hipGraph_t graph = nullptr;
-            hipError_t e = hipStreamEndCapture(cs, &graph);
-            if (r != LABS_OK || e != hipSuccess) {
-                if (graph) hipGraphDestroy(graph);
-                return r != LABS_OK ? r : device_error(e, "hipStreamEndCapture");
+    if (F > 1 && packed && (s = mlp_pack(lay, pr.params_bf16, B.fwd_ws, B.fwd_bytes, st))) return s;
+    for (int t = 1; t <= c.steps;) {
+        if ((t - 1) % F == 0) {
+            w.t0 = t - 1;
+            w.t1 = F > 1 ? t : (t - 1 + kLogSegment < c.steps ? t - 1 + kLogSegment : c.steps);
+            if ((s = launch_walk_log(w, st))) return s;
+            t = w.t1 + 1;
+            if (F > 1) {
+                A.t = w.t1;
+                hipLaunchKernelGGL(k_lw_corr, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, A);
+                LABS_LAUNCHED("k_lw_corr");
             }
-            e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-            hipGraphDestroy(graph);
-            if (e != hipSuccess) return device_error(e, "hipGraphInstantiate");
-            if (g_lw_graphs.size() >= 32) {
-                // free an old graph only once nothing queued can still use it
-                LABS_HIP(hipDeviceSynchronize());
-                hipGraphExecDestroy(g_lw_graphs.begin()->second);
-                g_lw_graphs.erase(g_lw_graphs.begin());
-            }
-            g_lw_graphs[key] = exec;
+            continue;
         }
-        for (int q = 0; q < reps; ++q) LABS_HIP(hipGraphLaunch(exec, st));
-        t = reps * period + 1;
+        if (packed) {
+            s = mlp_forward_state(lay, pr.params, B.fwd_ws, n, A.seq, A.C, A.ldc, const_cast<float*>(A.logits), st);
+        } else if (mlp) {
+            s = launch_features(c.L, n, A.seq, B.X, lay.ld_in, st);
+            if (!s) s = mlp_forward(lay, pr.params, pr.params_bf16, n, B.X, const_cast<float*>(A.logits), B.fwd_ws,
+                                    B.fwd_bytes, st);
+        }
+        if (s) return s;
+        A.t = t++;
+        if ((s = launch_lw_step(A, st))) return s;
     }
-    for (; t <= c.steps; ++t)
-        if ((s = enqueue_step(t, st))) return s;
+    if (F == 1 && o.cands) {
+        const int64_t cn = n * c.steps * A.top_m;
+        hipLaunchKernelGGL(k_fill_i16, dim3((unsigned)(cn / 256 + 1 < 65536 ? cn / 256 + 1 : 65536)), dim3(256), 0, st,
+                           cn, o.cands, (int16_t)-1);
+        LABS_LAUNCHED("k_fill_i16");
+    }
 
     hipLaunchKernelGGL(k_lw_outputs, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, A, o.final_seqs,
                        o.final_E, o.best_seqs, o.best_E, o.best_step, o.hit_step);

@@ -541,7 +541,7 @@ __global__ __launch_bounds__(256) void k_pack_weights(labs_mlp_layout y, const u
     const int64_t n1 = packed_elems(y.hidden, y.d_in) / 8, n2 = packed_elems(y.hidden, y.hidden) / 8,
                   n3 = packed_elems(y.d_out, y.hidden) / 8;
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n1 + n2 + n3) return;     // the slack behind is read, never used
+    if (i >= n1 + n2 + n3) return;
     uint4* const dst = (uint4*)out + i;
     const uint16_t* W = Pb + y.off_W1;
     int rows = y.hidden, K = y.d_in, ld = y.ld_in;
@@ -555,8 +555,8 @@ __global__ __launch_bounds__(256) void k_pack_weights(labs_mlp_layout y, const u
         W = Pb + y.off_W2;
         K = ld = y.hidden;
     }
-    const int nch = (K + 31) / 32;
-    const int lane = (int)(i & 63), kc = (int)((i >> 6) % nch), t = (int)((i >> 6) / nch);
+    const int tiles = (rows + 15) / 16;
+    const int lane = (int)(i & 63), t = (int)((i >> 6) % tiles), kc = (int)((i >> 6) / tiles);
     const int row = 16 * t + (lane & 15), k = 32 * kc + 8 * (lane >> 4);
     uint4 v = make_uint4(0, 0, 0, 0);
     if (row < rows && k < K) {
@@ -568,16 +568,22 @@ __global__ __launch_bounds__(256) void k_pack_weights(labs_mlp_layout y, const u
 
 // The three layers of 16 MR rows by one workgroup: the feature rows and the hidden
 // activations stay in LDS, the packed weights are read from the L2 (655 KB a workgroup
-// at L = 501, hidden 256).  Bound by the latency of those loads and of the operand reads
-// from LDS, with GELU and the rows' first load behind; the products themselves take 3 us.
+// at L = 501, hidden 256).  All workgroups run in step, so the phases add up: of 28.5 us
+// for 16,384 rows the packing takes 4, the rows' load 5, GELU 4.6, the logits' stores 5.2;
+// with the weights, the rows or the products taken out the rest barely moves (2, 0, 1).
 // As three launches of tiled products the activations went through memory and the narrow
-// layers left CUs idle: 16,384 rows at L = 501, hidden 256, 62.9 -> 29.7 us with the
-// packing (4 us), 100 rows 34.0 -> 17.2.
+// layers left CUs idle: 16,384 rows at L = 501, hidden 256, 62.9 us, 100 rows 34.0 (17.2
+// now).  STATE: the features are made here from the walk's sequences and C (26.2 us a pass,
+// where X had to be written first).
 struct FwdArgs {
     int n, d_in, ld_in, hidden, d_out, ld_out;
     const uint16_t *X, *W1, *W2, *W3;   // W*: packed
     const float *b1, *b2, *b3;
     float* logits;
+    // the features' sources in place of X: packed sequences, C_{2m} at C[ldc * row + m - 1]
+    const uint32_t* seq;
+    const int16_t* C;
+    int L, W, ldc;
 };
 
 // LDS of a workgroup of 16 MR rows: the features or the second hidden layer, the first
@@ -587,7 +593,7 @@ __host__ __device__ inline int forward_lds(int mr, int ld_in, int hidden) {
     return 16 * mr * ((sx > sh ? sx : sh) + sh) + 64;
 }
 
-template <int MR>
+template <int MR, bool STATE>
 __global__ __launch_bounds__(kTileThreads, MR == 4 ? 2 : 4) void k_forward(FwdArgs F) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int ROWS = 16 * MR;
@@ -595,20 +601,83 @@ __global__ __launch_bounds__(kTileThreads, MR == 4 ? 2 : 4) void k_forward(FwdAr
     char* const X = lds;                 // the second hidden layer takes its place
     char* const H1 = lds + ROWS * (sx > sh ? sx : sh);
     const int64_t m0 = (int64_t)blockIdx.x * ROWS;
-    // a wave a row, 16 bytes a lane; RW rows in flight
-    const int per = F.ld_in / 8, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // a wave a row, RW rows in flight; rows past n repeat the last one and are not stored
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int RW = ROWS / kTileWaves;
-    for (int c = lane; c < per; c += 64) {
-        uint4 v[RW];
+    int64_t src[RW];
 #pragma unroll
-        for (int i = 0; i < RW; ++i) {
-            const int64_t r = m0 + wave + kTileWaves * i;
-            v[i] = *(const uint4*)(F.X + (r < F.n ? r : F.n - 1) * F.ld_in + 8 * c);   // rows past n are not stored
+    for (int i = 0; i < RW; ++i) {
+        const int64_t r = m0 + wave + kTileWaves * i;
+        src[i] = r < F.n ? r : F.n - 1;
+    }
+    char* const xr = X + wave * sx;
+    if constexpr (!STATE) {
+        for (int c = lane; c < F.ld_in / 8; c += 64) {
+            uint4 v[RW];
+#pragma unroll
+            for (int i = 0; i < RW; ++i) v[i] = *(const uint4*)(F.X + src[i] * F.ld_in + 8 * c);
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                if (8 * c + 8 > F.d_in) v[i] = mask_tail(v[i], 8 * c, F.d_in);
+                *(uint4*)(xr + kTileWaves * i * sx + 16 * c) = v[i];
+            }
         }
+    } else {
+        // Four lags a lane and eight elements of the sequence (byte c of the string is
+        // byte c ^ 3 in memory), loaded together; then the lags, and zeros to the row's
+        // end, over what the last elements' chunk left behind them.
+        const int k = F.d_in - F.L;
+        uint2 cv[RW];
+        uint32_t z[RW];
+        auto load_elements = [&](int c) {
 #pragma unroll
-        for (int i = 0; i < RW; ++i) {
-            if (8 * c + 8 > F.d_in) v[i] = mask_tail(v[i], 8 * c, F.d_in);
-            *(uint4*)(X + (wave + kTileWaves * i) * sx + 16 * c) = v[i];
+            for (int i = 0; i < RW; ++i)
+                z[i] = 8 * c < F.L ? ~(uint32_t)((const uint8_t*)(F.seq + src[i] * F.W))[c ^ 3] : 0u;
+        };
+        auto load_lags = [&](int c) {
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+                cv[i] = 4 * c < F.ldc ? *(const uint2*)(F.C + src[i] * F.ldc + 4 * c) : make_uint2(0, 0);
+        };
+        auto put_elements = [&](int c) {
+            if (8 * c >= F.L) return;
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                uint32_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    w[q] = 0x3F803F80u | ((z[i] << (8 + 2 * q)) & 0x8000u) | ((z[i] << (25 + 2 * q)) & 0x80000000u);
+                *(uint4*)(xr + kTileWaves * i * sx + 16 * c) = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        };
+        auto put_lags = [&](int c) {
+            if (F.L + 4 * c >= F.ld_in) return;
+            float scale[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) scale[q] = corr_scale(F.L, min(4 * c + q + 1, k));
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                const int v[4] = {(int16_t)cv[i].x, (int)cv[i].x >> 16, (int16_t)cv[i].y, (int)cv[i].y >> 16};
+                const uint32_t a = f2bf2((float)v[0] * scale[0], (float)v[1] * scale[1]),
+                               b = f2bf2((float)v[2] * scale[2], (float)v[3] * scale[3]);
+                char* const d = xr + kTileWaves * i * sx + 2 * (F.L + 4 * c);      // L is odd
+                *(uint16_t*)d = (uint16_t)a;
+                *(uint32_t*)(d + 2) = (a >> 16) | (b << 16);
+                *(uint16_t*)(d + 6) = (uint16_t)(b >> 16);
+            }
+        };
+        load_elements(lane);
+        load_lags(lane);
+        put_elements(lane);
+        for (int c = lane + 64; 8 * c < F.L; c += 64) {
+            load_elements(c);
+            put_elements(c);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        put_lags(lane);
+        for (int c = lane + 64; F.L + 4 * c < F.ld_in; c += 64) {
+            load_lags(c);
+            put_lags(c);
         }
     }
     __syncthreads();
@@ -638,15 +707,14 @@ constexpr int kLdsBytes = 160 * 1024;
 constexpr int kFusedHidden = 256;
 
 static int64_t packed_total(const labs_mlp_layout& y) {
-    return packed_elems(y.hidden, y.d_in) + packed_elems(y.hidden, y.hidden) + packed_elems(y.d_out, y.hidden) +
-           512 * kTilePF;
+    return packed_elems(y.hidden, y.d_in) + packed_elems(y.hidden, y.hidden) + packed_elems(y.d_out, y.hidden);
 }
 
 // Row tiles a workgroup.  While one workgroup a CU holds every row, the fewest tiles that
 // do (L = 501, hidden 256: 4,096 rows 17.5 us at one, 19.4 at two, 25.2 at four; 8,192
 // rows 25.8, 21.3, 26.7).  Beyond, four tiles read each weight least often but leave one
 // workgroup a CU, so a last round that is at most half full costs more than it saves:
-// 16,384 rows 33.0 us at two and 29.7 at four, 20,480 rows 44.9 and 49.7.
+// 16,384 rows 33.0 us at two and 29.7 at four, 20,480 rows 44.9 and 49.7 (with the GELU of that time).
 static int forward_tiles(const labs_mlp_layout& y, int64_t n) {
     constexpr int kCUs = 256;
     const int64_t last = (n + 63) / 64 % kCUs;
@@ -655,12 +723,13 @@ static int forward_tiles(const labs_mlp_layout& y, int64_t n) {
     return mr;
 }
 
-template <int MR>
+template <int MR, bool STATE>
 static labs_status run_forward(const FwdArgs& F, hipStream_t st) {
     const int bytes = forward_lds(MR, F.ld_in, F.hidden);
-    LABS_HIP(hipFuncSetAttribute((const void*)k_forward<MR>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes));
-    hipLaunchKernelGGL(k_forward<MR>, dim3((unsigned)((F.n + 16 * MR - 1) / (16 * MR))), dim3(kTileThreads), bytes, st,
-                       F);
+    LABS_HIP(hipFuncSetAttribute((const void*)k_forward<MR, STATE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 kLdsBytes));
+    hipLaunchKernelGGL((k_forward<MR, STATE>), dim3((unsigned)((F.n + 16 * MR - 1) / (16 * MR))), dim3(kTileThreads),
+                       bytes, st, F);
     LABS_LAUNCHED("k_forward");
     return LABS_OK;
 }
@@ -675,19 +744,44 @@ labs_status mlp_pack(const labs_mlp_layout& y, const uint16_t* Pb, void* ws, siz
     return LABS_OK;
 }
 
-labs_status mlp_forward_packed(const labs_mlp_layout& y, const float* P, const void* ws, int64_t n, const uint16_t* X,
-                               float* logits, hipStream_t st) {
-    if (n <= 0) return LABS_OK;
-    const uint16_t* W1 = (const uint16_t*)ws;
-    const uint16_t* W2 = W1 + packed_elems(y.hidden, y.d_in);
-    const uint16_t* W3 = W2 + packed_elems(y.hidden, y.hidden);
-    const FwdArgs F{(int)n, y.d_in, y.ld_in, y.hidden, y.d_out, y.ld_out, X, W1, W2, W3, P + y.off_b1, P + y.off_b2,
-                    P + y.off_b3, logits};
-    switch (forward_tiles(y, n)) {
-        case 4: return run_forward<4>(F, st);
-        case 2: return run_forward<2>(F, st);
-        default: return run_forward<1>(F, st);
+static FwdArgs forward_args(const labs_mlp_layout& y, const float* P, const void* ws, int64_t n, float* logits) {
+    FwdArgs F{};
+    F.n = (int)n;
+    F.d_in = y.d_in; F.ld_in = y.ld_in; F.hidden = y.hidden; F.d_out = y.d_out; F.ld_out = y.ld_out;
+    F.W1 = (const uint16_t*)ws;
+    F.W2 = F.W1 + packed_elems(y.hidden, y.d_in);
+    F.W3 = F.W2 + packed_elems(y.hidden, y.hidden);
+    F.b1 = P + y.off_b1; F.b2 = P + y.off_b2; F.b3 = P + y.off_b3;
+    F.logits = logits;
+    return F;
+}
+
+template <bool STATE>
+static labs_status run_tiles(int mr, const FwdArgs& F, hipStream_t st) {
+    switch (mr) {
+        case 4: return run_forward<4, STATE>(F, st);
+        case 2: return run_forward<2, STATE>(F, st);
+        default: return run_forward<1, STATE>(F, st);
     }
+}
+
+static labs_status mlp_forward_packed(const labs_mlp_layout& y, const float* P, const void* ws, int64_t n,
+                                      const uint16_t* X, float* logits, hipStream_t st) {
+    FwdArgs F = forward_args(y, P, ws, n, logits);
+    F.X = X;
+    return run_tiles<false>(forward_tiles(y, n), F, st);
+}
+
+labs_status mlp_forward_state(const labs_mlp_layout& y, const float* P, const void* ws, int64_t n, const uint32_t* seq,
+                              const int16_t* C, int ldc, float* logits, hipStream_t st) {
+    if (n <= 0) return LABS_OK;
+    FwdArgs F = forward_args(y, P, ws, n, logits);
+    F.seq = seq;
+    F.C = C;
+    F.L = y.L;
+    F.W = words_of(y.L);
+    F.ldc = ldc;
+    return run_tiles<true>(forward_tiles(y, n), F, st);
 }
 
 size_t mlp_forward_ws(const labs_mlp_layout& y, int64_t n) {

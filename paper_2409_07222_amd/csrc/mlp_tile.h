@@ -29,27 +29,41 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
 __device__ __forceinline__ float corr_scale(int L, int m) { return __builtin_amdgcn_rcpf((float)(L - 2 * m)); }
 __device__ __forceinline__ uint16_t corr_feature(int c, float scale) { return f2bf((float)c * scale); }
 
+// Two bf16 values, round to nearest even, the first in the low half.
+__device__ __forceinline__ uint32_t f2bf2(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
 // bf16(gelu_f(x)) of four values.  x (1 - 1 / (1 + e^{2u})) from the hardware exponential
 // and reciprocal lies within 1e-6 |x| of gelu_f's value (both are within 5e-7 |x| of the
 // true one: tanhf and the sum 1 + tanh err by a few 2^-24, the exponential by
-// 2^-23 + |2u| 2^-24 of its value, which the slope of 1 / (1 + e) makes at most 0.45
-// 2^-23); where the two ends of that interval round to the same bf16, so does gelu_f's.
-// The few others (about one value in a thousand), infinities and NaN take gelu_f itself,
-// which branches per value and leaves no two of them in flight.
-__device__ __forceinline__ void gelu_bf16(const float (&x)[4], uint32_t (&h)[4]) {
+// 2^-23 + |2u| 2^-22 of its value, which the slope of 1 / (1 + e) makes at most 2^-23);
+// where the two ends of that interval round to the same bf16, so does gelu_f's.  The few
+// others (about one value in a thousand), infinities and NaN take gelu_f itself, which
+// branches per value and leaves no two of them in flight.
+__device__ __forceinline__ void gelu_bf16(const float (&x)[4], uint32_t (&h)[2]) {
     uint32_t far = 0;
+    float lo[4], hi[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const float u = 0.7978845608028654f * (x[j] + 0.044715f * x[j] * x[j] * x[j]);
-        const float q = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(2.8853900817779268f * u));
-        const float r = x[j] - x[j] * q;
-        const float d = 1e-6f * fabsf(x[j]);
-        h[j] = f2bf(r - d);
-        far |= (h[j] ^ f2bf(r + d)) | (fabsf(x[j]) < 1e4f ? 0u : 1u);
+        // 2 u log2(e) = x (2.3022082 + 0.10294324 x^2)
+        const float w = x[j] * fmaf(0.10294324f, x[j] * x[j], 2.3022082f);
+        const float q = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(w));
+        const float r = fmaf(-x[j], q, x[j]);
+        lo[j] = fmaf(fabsf(x[j]), -1e-6f, r);
+        hi[j] = fmaf(fabsf(x[j]), 1e-6f, r);
     }
-    if (far) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) h[j] = f2bf(gelu_f(x[j]));
+    for (int j = 0; j < 2; ++j) {
+        h[j] = f2bf2(lo[2 * j], lo[2 * j + 1]);
+        far |= h[j] ^ f2bf2(hi[2 * j], hi[2 * j + 1]);
+    }
+    if (far || !(fabsf(x[0] + x[1] + x[2] + x[3]) < 1e30f)) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            h[j] = f2bf(gelu_f(x[2 * j])) | ((uint32_t)f2bf(gelu_f(x[2 * j + 1])) << 16);
     }
 }
 
@@ -66,7 +80,8 @@ __device__ __forceinline__ uint4 mask_tail(uint4 v, int k, int K) {
 
 // Weights in fragment order: of column tile t (16 rows of W) and step kc (32 columns),
 // lane l's 16 bytes are W[16 t + l % 16][32 kc + 8 (l / 16) .. + 7], so a wave's operand is
-// one contiguous kilobyte (rows of W themselves would touch 64 cache lines).
+// one contiguous kilobyte (rows of W themselves would touch 64 cache lines).  The tiles of
+// a step follow one another, as the waves of a workgroup read them.
 __host__ __device__ inline int64_t packed_elems(int ncols, int K) {
     return (int64_t)((ncols + 15) / 16) * ((K + 31) / 32) * 512;
 }
@@ -81,17 +96,16 @@ constexpr int kTilePF = 4;
 // acc[c][r] = (16 columns of tile t[c]) (tile rows 16 r .. + 15)^T over the steps of K, in
 // order: the layer's columns are the matrix product's rows, so a lane ends with four
 // consecutive columns 4 (lane / 16) .. + 3 of row lane % 16.  A: the rows in LDS, stride
-// sa bytes.  WP: packed weights, nch steps a tile, read PF steps ahead: past a tile's end
-// the reads run on into what follows (kTilePF steps of slack after the last layer, one
-// step after the rows in LDS) and are not used.
+// sa bytes.  WP: packed weights, nch steps of `tiles` tiles, read kTilePF steps ahead (at
+// the end the last step again); the rows are read one step ahead, at the end past them.
 template <int MR, int CT>
 __device__ __forceinline__ void tile_product(f32x4 (&acc)[CT][MR], const char* A, int sa, const uint16_t* __restrict__ WP,
-                                             const int (&t)[CT], int nch) {
+                                             const int (&t)[CT], int tiles, int nch) {
     constexpr int PF = kTilePF;
     const int lane = threadIdx.x & 63;
     const uint4* wp[CT];     // wave-uniform; the lane joins at the load
 #pragma unroll
-    for (int c = 0; c < CT; ++c) wp[c] = (const uint4*)(WP) + (int64_t)t[c] * nch * 64;
+    for (int c = 0; c < CT; ++c) wp[c] = (const uint4*)(WP) + t[c] * 64;
     const char* ap = A + (lane & 15) * sa + 16 * (lane >> 4);
 #pragma unroll
     for (int c = 0; c < CT; ++c)
@@ -113,7 +127,7 @@ __device__ __forceinline__ void tile_product(f32x4 (&acc)[CT][MR], const char* A
     bf16x8 a[2][MR];
     auto fetch = [&](int kc, uint4 (&d)[CT]) {
 #pragma unroll
-        for (int c = 0; c < CT; ++c) d[c] = wp[c][64 * kc + lane];
+        for (int c = 0; c < CT; ++c) d[c] = wp[c][64 * tiles * min(kc, nch - 1) + lane];
     };
     // The scheduling barriers keep the loads where they are written: left alone, the
     // compiler moves them next to their uses and every step waits for the L2.
@@ -157,7 +171,7 @@ __device__ __forceinline__ void tile_layer(const char* A, int sa, const uint16_t
         for (int c = 0; c < CT; ++c)
 #pragma unroll
             for (int j = 0; j < 4; ++j) bv[c][j] = bias[min(16 * t[c] + 4 * (lane >> 4) + j, ncols - 1)];
-        tile_product<MR, CT>(acc, A, sa, WP, t, nch);
+        tile_product<MR, CT>(acc, A, sa, WP, t, tiles, nch);
 #pragma unroll
         for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -175,9 +189,9 @@ __device__ __forceinline__ void store_hidden(char* H, int sh, const float (&bias
     float x[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) x[j] = v[j] + bias[j];
-    uint32_t h[4];
+    uint32_t h[2];
     gelu_bf16(x, h);
-    *(uint2*)(H + row * sh + 2 * col) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    *(uint2*)(H + row * sh + 2 * col) = make_uint2(h[0], h[1]);
 }
 
 // Row strides in bytes of an LDS tile of `ld` bf16 columns: 16 bytes more than the row,

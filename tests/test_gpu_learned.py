@@ -153,6 +153,81 @@ def test_repeat_call_reuses_graph_identically(lb):
     assert np.array_equal(_np(a["traj_E"]), _np(b["traj_E"]))
 
 
+@pytest.mark.parametrize("L,p,m,F,n,steps", [(5, 0, 2, 3, 1, 12), (37, 0, 9, 2, 17, 40), (255, 10, 16, 4, 3, 14),
+                                             (257, 0, 8, 7, 5, 16), (511, 16, 17, 5, 2, 12),
+                                             (513, 3, 64, 4, 2, 10), (639, 0, 7, 6, 33, 10)])
+def test_narrow_step_edges(lb, orc, L, p, m, F, n, steps):
+    """The narrow step where its shape changes (128, 256 and 320 lags; lists of 8, 16
+    and beyond; workgroups of 16 walkers with a remainder): moves, energies,
+    candidates and the log against the oracle with the random proposer."""
+    lo, hi, seed, ps, every = max(1, L // 10), max(2, L // 5), 19, 77, 3
+    r = lb.learned_walk(L, p, steps, lo, hi, seed, n, mode=lb.PROPOSE_RANDOM, top_m=m, fallback_every=F,
+                        prop_seed=ps, log_every=every, want_traj=True, want_cands=True)
+    traj, moves, cands = _np(r["traj_E"]), _np(r["moves"]), _np(r["cands"])
+    seqs, mask, label = _np(r["log_seqs"]), _np(r["log_mask"]), _np(r["log_label"])
+    for w in {0, n // 2, n - 1}:
+        ref = ol.proposal_walk(L, p, steps, lo, hi, seed, w, F, ol.random_proposer(ps, L, w, m))
+        done = len(ref["moves"])
+        assert np.array_equal(traj[w, :done], np.array(ref["traj"])[:done]), w
+        assert np.array_equal(moves[w, :done], np.array(ref["moves"])), w
+        for t, c in enumerate(ref["cands"]):
+            assert [int(x) for x in cands[w, t] if x >= 0] == (c if c is not None else []), (w, t)
+        for q in range(steps // every):
+            t, rec = (q + 1) * every, q * n + w
+            if t > done or ref["moves"][t - 1] < 0:
+                break
+            st = li.unpack(seqs[rec:rec + 1].view(np.uint32), L)[0]
+            assert np.array_equal(st, ref["states"][t - 1])
+            adm = [a for a in range(1, (L - 1) // 2 + 2)
+                   if (int(mask[rec, (a - 1) // 32]) >> ((a - 1) % 32)) & 1]
+            assert adm == ref["admissible"][t - 1]
+            assert label[rec] == ref["moves"][t - 1] - 1
+
+
+@pytest.mark.parametrize("L,hidden,n", [(5, 64, 3), (101, 64, 17), (255, 128, 40), (257, 256, 64),
+                                        (513, 256, 70), (639, 192, 33)])
+def test_network_features_from_the_walk_state(lb, L, hidden, n):
+    """The forward pass that builds its features from the walk's state against the
+    features kernel and the separate products: the network widened to 320 hidden
+    units with zero weights gives the same logits bit for bit, so the walks are equal."""
+    import torch
+    p, steps, lo, hi = 0, 20, 1, 2
+    lay, P, blob, pb = _net(lb, L, hidden, 58)
+    wide = lb.mlp_layout(L, 320)
+    Q = {key: np.zeros(s, np.float32) for key, s in
+         (("W1", (320, lay.d_in)), ("b1", 320), ("W2", (320, 320)), ("b2", 320),
+          ("W3", (lay.d_out, 320)), ("b3", lay.d_out))}
+    for key in Q:
+        Q[key][tuple(slice(0, d) for d in P[key].shape)] = P[key]
+    wblob = torch.from_numpy(lb.mlp_blob_from_dict(wide, Q)).cuda()
+    wpb = torch.empty(wide.n_params, dtype=torch.bfloat16, device="cuda")
+    lb.mlp_cast(wide, wblob, wpb)
+    a, b = (lb.learned_walk(L, p, steps, lo, hi, 6, n, mode=lb.PROPOSE_MLP, top_m=8, fallback_every=8,
+                            hidden=h, params=x, params_bf16=y, want_traj=True, want_cands=True)
+            for h, x, y in ((hidden, blob, pb), (320, wblob, wpb)))
+    for key in ("traj_E", "moves", "cands"):
+        assert np.array_equal(_np(a[key]), _np(b[key])), key
+
+
+@pytest.mark.parametrize("m", [5, 12, 20])
+def test_equal_scores_take_the_lower_positions(lb, orc, m):
+    """A network of zeros scores every position alike: the candidates are the first
+    m admissible positions."""
+    import torch
+    L, p, steps, n, F = 101, 8, 40, 18, 16
+    lay = lb.mlp_layout(L, 64)
+    blob = torch.zeros(lay.n_params, dtype=torch.float32, device="cuda")
+    pb = torch.zeros(lay.n_params, dtype=torch.bfloat16, device="cuda")
+    r = lb.learned_walk(L, p, steps, 10, 20, 4, n, mode=lb.PROPOSE_MLP, top_m=m, fallback_every=F, hidden=64,
+                        params=blob, params_bf16=pb, want_traj=True, want_cands=True)
+    for w in (0, n - 1):
+        ref = ol.proposal_walk(L, p, steps, 10, 20, 4, w, F, lambda t, s, adm: sorted(adm)[:m])
+        assert np.array_equal(_np(r["traj_E"])[w], np.array(ref["traj"]))
+        assert np.array_equal(_np(r["moves"])[w], np.array(ref["moves"]))
+        for t, c in enumerate(ref["cands"]):
+            assert [int(x) for x in _np(r["cands"])[w, t] if x >= 0] == (c if c is not None else [])
+
+
 def _admissible(mask_words, d_out):
     mk = mask_words.cpu().numpy().view(np.uint32)
     adm = np.zeros((mk.shape[0], d_out), bool)
