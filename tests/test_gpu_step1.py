@@ -62,6 +62,30 @@ def test_flip_deltas_skew(lb, orc, L, p):
         assert np.array_equal(dE[j], orc.deltas_skew(S[j], p))
 
 
+@pytest.mark.parametrize("L", [1, 16, 17, 31, 32, 33, 48, 49, 255, 256, 257, 511, 513, 767, 768, 769, 1008, 1009, 1023])
+def test_flip_deltas_edges(lb, orc, L):
+    """Word, 16-element, 64-element and tile edges of the flips' products; the constant
+    sequences reach the largest C (two bytes), and bits behind the last element are
+    not read."""
+    S = np.concatenate([li.random_pm1(5 * L, 4, L), np.ones((1, L), np.int8), -np.ones((1, L), np.int8)])
+    words = li.pack(S).view(np.uint32).copy()
+    if L % 32:
+        words[:, -1] |= np.uint32(0xFFFFFFFF >> (L % 32))
+    E, C = lb.energy(L, _dev(words), want_c=True)
+    Eo, Co = orc.energy_batch(S, with_c=True)
+    assert np.array_equal(E.cpu().numpy(), Eo)
+    if L > 1:
+        assert np.array_equal(C.cpu().numpy(), Co)
+    dE = lb.flip_deltas(L, _dev(words)).cpu().numpy()
+    for j in range(len(S)):
+        assert np.array_equal(dE[j], orc.deltas_single(S[j]))
+    if L % 2 and L >= 3:
+        for p in {0, (L - 1) // 4, (L - 1) // 2}:
+            dE = lb.flip_deltas(L, _dev(words), skew=True, p=p).cpu().numpy()
+            for j in range(len(S)):
+                assert np.array_equal(dE[j], orc.deltas_skew(S[j], p))
+
+
 def test_cfg1_exhaustive(lb, orc):
     """All 2^19 skew-symmetric sequences at L = 37: min E and its argmin set."""
     L = 37
