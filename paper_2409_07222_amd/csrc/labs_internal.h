@@ -290,6 +290,17 @@ labs_status mlp_grads(const labs_mlp_layout& y, const float* P, const uint16_t* 
 labs_status mlp_adam(const labs_mlp_layout& y, float* P, uint16_t* Pb, const float* G, float* M, float* V, int t,
                      double lr, double b1, double b2, double eps, hipStream_t st);
 labs_status mlp_cast(const labs_mlp_layout& y, const float* P, uint16_t* Pb, hipStream_t st);
+// Gradients, and with `adam` the update, of a network that packs (mlp_train.hip), n > 0:
+// from packed sequences, or with seqs null from the features X.
+struct MlpAdam {
+    float *M, *V;
+    int t;
+    double lr, b1, b2, eps;
+};
+size_t mlp_train_ws(const labs_mlp_layout& y, int64_t n);
+labs_status mlp_train(const labs_mlp_layout& y, float* P, uint16_t* Pb, int64_t n, const uint32_t* seqs,
+                      const uint16_t* X, const uint32_t* mask, const int32_t* labels, float* G, float* loss,
+                      const MlpAdam* adam, void* ws, size_t wsb, hipStream_t st);
 
 // First-step walk with a proposer (learned.hip).
 labs_status validate_step1_cfg(const labs_step1_cfg& c);

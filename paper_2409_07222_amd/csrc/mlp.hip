@@ -296,8 +296,6 @@ __global__ __launch_bounds__(256) void k_gemm_nt128(int M, int N, int K, const u
 
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-constexpr int kMaxSplits = 16;
-
 // C = A B with the epilogue `epi`.  128x128 tiles when the grid still holds two
 // workgroups per CU, else 64x64 tiles; plain FP32 products over a long K whose
 // grid is small (weight gradients: K is the batch) are split over K into
@@ -317,12 +315,8 @@ labs_status gemm(bool a_k, bool b_k, int M, int N, int K, const uint16_t* A, int
     const long long tiles = (long long)((M + GT - 1) / GT) * ((N + GT - 1) / GT);
     int splits = 1, kchunk = (K + GK - 1) / GK * GK;
     Epi e = epi;
-    if (epi.kind == EPI_F32 && split_ws && tiles < 512 && K >= 2 * 256) {
-        splits = (int)((512 + tiles - 1) / tiles);
-        if (splits > kMaxSplits) splits = kMaxSplits;
-        if (splits > K / 256) splits = K / 256;
-        kchunk = ((K + splits - 1) / splits + GK - 1) / GK * GK;
-        splits = (K + kchunk - 1) / kchunk;
+    if (epi.kind == EPI_F32 && split_ws) splits = product_splits(tiles, K, &kchunk);
+    if (splits > 1) {
         e.out_f = split_ws;
         e.ldf = N;
         e.zstride = (int64_t)M * N;
@@ -442,7 +436,6 @@ __global__ __launch_bounds__(256) void k_mean(int64_t n, const float* __restrict
 
 // Column sums of an fp32 [rows x cols] matrix (row stride ld) in two passes:
 // partial sums over row chunks, then a fixed-order sum of the partials.
-constexpr int kColChunks = 64;
 __global__ __launch_bounds__(256) void k_colsum_part(int64_t rows, int cols, int64_t ld, const float* __restrict__ D,
                                                      float* __restrict__ part) {
     __shared__ float red[4][64];
@@ -471,25 +464,12 @@ __global__ __launch_bounds__(256) void k_fill_f32(int64_t n, float* __restrict__
 }
 
 // ------------------------------------------------------------------ Adam
-// Kingma and Ba (2015), FP32 masters; every operation rounded separately
-// (contraction into FMAs is switched off) so that a float32 host computation
-// in the same order matches bit for bit.
 __global__ __launch_bounds__(256) void k_adam(int64_t n, float* __restrict__ P, uint16_t* __restrict__ Pb,
                                               const float* __restrict__ G, float* __restrict__ M, float* __restrict__ V,
                                               float b1, float omb1, float b2, float omb2, float bc1, float bc2,
                                               float lr, float eps) {
-#pragma clang fp contract(off)
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const float g = G[i];
-        const float m = b1 * M[i] + omb1 * g;
-        const float v = b2 * V[i] + (omb2 * g) * g;
-        M[i] = m;
-        V[i] = v;
-        const float mh = m / bc1, vh = v / bc2;
-        const float p = P[i] - (lr * mh) / (sqrtf(vh) + eps);   // sqrtf and '/' are correctly rounded
-        P[i] = p;
-        Pb[i] = f2bf(p);
-    }
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        adam_update(i, G[i], P, Pb, M, V, b1, omb1, b2, omb2, bc1, bc2, lr, eps);
 }
 
 __global__ __launch_bounds__(256) void k_cast_bf16(int64_t n, const float* __restrict__ P, uint16_t* __restrict__ Pb) {
@@ -535,35 +515,15 @@ labs_status launch_features(int L, int64_t n, const uint32_t* seqs, uint16_t* X,
 }
 
 // ------------------------------------------------------------------ forward pass
-// Packs W1, W2 and W3 into fragment order (zeros beyond each layer's rows and columns).
+// Packs W1, W2 and W3 into fragment order, one behind the other.
 __global__ __launch_bounds__(256) void k_pack_weights(labs_mlp_layout y, const uint16_t* __restrict__ Pb,
                                                       uint16_t* __restrict__ out) {
-    const int64_t n1 = packed_elems(y.hidden, y.d_in) / 8, n2 = packed_elems(y.hidden, y.hidden) / 8,
-                  n3 = packed_elems(y.d_out, y.hidden) / 8;
+    const int H = y.hidden;
+    const int64_t n1 = packed_elems(H, y.d_in), n2 = packed_elems(H, H), n3 = packed_elems(y.d_out, H);
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n1 + n2 + n3) return;
-    uint4* const dst = (uint4*)out + i;
-    const uint16_t* W = Pb + y.off_W1;
-    int rows = y.hidden, K = y.d_in, ld = y.ld_in;
-    if (i >= n1 + n2) {
-        i -= n1 + n2;
-        W = Pb + y.off_W3;
-        rows = y.d_out;
-        K = ld = y.hidden;
-    } else if (i >= n1) {
-        i -= n1;
-        W = Pb + y.off_W2;
-        K = ld = y.hidden;
-    }
-    const int tiles = (rows + 15) / 16;
-    const int lane = (int)(i & 63), t = (int)((i >> 6) % tiles), kc = (int)((i >> 6) / tiles);
-    const int row = 16 * t + (lane & 15), k = 32 * kc + 8 * (lane >> 4);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (row < rows && k < K) {
-        v = *(const uint4*)(W + (int64_t)row * ld + k);
-        if (k + 8 > K) v = mask_tail(v, k, K);
-    }
-    *dst = v;
+    if (i < n1 / 8) return pack_chunk<false>(out, Pb + y.off_W1, H, y.d_in, y.ld_in, i);
+    if ((i -= n1 / 8) < n2 / 8) return pack_chunk<false>(out + n1, Pb + y.off_W2, H, H, H, i);
+    if ((i -= n2 / 8) < n3 / 8) pack_chunk<false>(out + n1 + n2, Pb + y.off_W3, y.d_out, H, H, i);
 }
 
 // The three layers of 16 MR rows by one workgroup: the feature rows and the hidden
@@ -823,6 +783,7 @@ labs_status mlp_forward(const labs_mlp_layout& y, const float* P, const uint16_t
 }
 
 size_t mlp_grads_ws(const labs_mlp_layout& y, int64_t n) {
+    if (mlp_packs(y)) return mlp_train_ws(y, n);
     const size_t H = (size_t)n * y.hidden, O = (size_t)n * y.ld_out;
     size_t b = 0;
     auto add = [&](size_t bytes) { b += align_up(bytes, 256); };
@@ -847,6 +808,16 @@ static labs_status colsum(int64_t rows, int cols, int64_t ld, const float* D, fl
 labs_status mlp_grads(const labs_mlp_layout& y, const float* P, const uint16_t* Pb, int64_t n, const uint16_t* X,
                       const uint32_t* mask, const int32_t* labels, float* G, float* loss, void* ws, size_t wsb,
                       hipStream_t st) {
+    if (n > 0 && mlp_packs(y))
+        return mlp_train(y, const_cast<float*>(P), const_cast<uint16_t*>(Pb), n, nullptr, X, mask, labels, G, loss,
+                         nullptr, ws, wsb, st);
+    hipLaunchKernelGGL(k_fill_f32, dim3(grid_for(y.n_params)), dim3(256), 0, st, y.n_params, G, 0.f);
+    LABS_LAUNCHED("k_fill_f32");
+    if (n <= 0) {
+        hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, st, (int64_t)1, loss, 0.f);
+        LABS_LAUNCHED("k_fill_f32");
+        return LABS_OK;
+    }
     Carve cv(ws, wsb);
     const size_t H = (size_t)n * y.hidden, O = (size_t)n * y.ld_out;
     float* a1 = cv.take<float>(H);
@@ -865,13 +836,6 @@ labs_status mlp_grads(const labs_mlp_layout& y, const float* P, const uint16_t* 
     float* splitw = cv.take<float>((size_t)kMaxSplits * y.hidden * (y.ld_in > y.hidden ? y.ld_in : y.hidden));
     if (!cv.ok() || !splitw) return LABS_E_NOMEM;
 
-    hipLaunchKernelGGL(k_fill_f32, dim3(grid_for(y.n_params)), dim3(256), 0, st, y.n_params, G, 0.f);
-    LABS_LAUNCHED("k_fill_f32");
-    if (n <= 0) {
-        hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, st, (int64_t)1, loss, 0.f);
-        LABS_LAUNCHED("k_fill_f32");
-        return LABS_OK;
-    }
     const int Hd = y.hidden;
     // forward, keeping pre-activations
     Epi e{};

@@ -35,6 +35,11 @@ labs_status check_adam(int32_t t, double lr, double b1, double b2, double eps) {
     return LABS_OK;
 }
 
+// The feature rows of a training step; a network that packs makes them in its kernel.
+size_t train_features_bytes(const labs_mlp_layout& y, int64_t n) {
+    return mlp_packs(y) ? 0 : align_up((size_t)n * y.ld_in * 2, 256);
+}
+
 labs_status check_learned(const labs_step1_cfg* cfg, const labs_proposer* pr) {
     if (!cfg || !pr) return invalid("cfg and prop must not be NULL");
     if (labs_status s = validate_step1_cfg(*cfg)) return s;
@@ -169,7 +174,7 @@ labs_status labs_mlp_train_workspace(const labs_mlp_layout* lay, int64_t n, size
     if (labs_status s = check_layout(lay)) return s;
     if (labs_status s = check_rows(n)) return s;
     if (!bytes) return invalid("bytes must not be NULL");
-    *bytes = align_up((size_t)n * lay->ld_in * 2, 256) + mlp_grads_ws(*lay, n);
+    *bytes = train_features_bytes(*lay, n) + mlp_grads_ws(*lay, n);
     return LABS_OK;
 }
 
@@ -184,9 +189,14 @@ labs_status labs_mlp_train_step(const labs_mlp_layout* lay, float* params, uint1
     if (!params || !params_bf16 || !grads || !m || !v || !loss || !ws) return invalid("pointers must not be NULL");
     if (n > 0 && (!seqs || !mask || !labels)) return invalid("seqs, mask and labels must not be NULL");
     if (!aligned16(params_bf16)) return invalid("params_bf16 must be 16-byte aligned");
-    const size_t xb = align_up((size_t)n * lay->ld_in * 2, 256);
+    const size_t xb = train_features_bytes(*lay, n);
     if (ws_bytes < xb + mlp_grads_ws(*lay, n)) return invalid("workspace too small");
     if (!aligned16(ws)) return invalid("workspace must be 16-byte aligned");
+    if (mlp_packs(*lay) && n > 0) {
+        const MlpAdam adam{m, v, t, lr, beta1, beta2, eps};
+        return mlp_train(*lay, params, params_bf16, n, seqs, nullptr, mask, labels, grads, loss, &adam, ws, ws_bytes,
+                         S(stream));
+    }
     uint16_t* X = (uint16_t*)ws;
     labs_status s = launch_features(lay->L, n, seqs, X, lay->ld_in, S(stream));
     if (s) return s;

@@ -67,6 +67,42 @@ __device__ __forceinline__ void gelu_bf16(const float (&x)[4], uint32_t (&h)[2])
     }
 }
 
+// Adam (Kingma and Ba 2015) of parameter i, FP32 masters; every operation rounded
+// separately (contraction into FMAs is switched off) so that a float32 host computation
+// in the same order matches bit for bit.
+__device__ __forceinline__ void adam_update(int64_t i, float g, float* __restrict__ P, uint16_t* __restrict__ Pb,
+                                            float* __restrict__ M, float* __restrict__ V, float b1, float omb1,
+                                            float b2, float omb2, float bc1, float bc2, float lr, float eps) {
+#pragma clang fp contract(off)
+    const float m = b1 * M[i] + omb1 * g;
+    const float v = b2 * V[i] + (omb2 * g) * g;
+    M[i] = m;
+    V[i] = v;
+    const float mh = m / bc1, vh = v / bc2;
+    const float p = P[i] - (lr * mh) / (sqrtf(vh) + eps);   // sqrtf and '/' are correctly rounded
+    P[i] = p;
+    Pb[i] = f2bf(p);
+}
+
+// Chunks of rows of a bias gradient's sum.
+constexpr int kColChunks = 64;
+
+// Splits of a weight gradient's sum over K rows when its output has `tiles` 64 x 64 tiles,
+// and the rows of each: enough for two workgroups a CU, at least 256 rows.
+constexpr int kMaxSplits = 16;
+inline int product_splits(long long tiles, int K, int* chunk) {
+    int splits = 1;
+    *chunk = (K + 31) / 32 * 32;
+    if (tiles < 512 && K >= 2 * 256) {
+        splits = (int)((512 + tiles - 1) / tiles);
+        if (splits > kMaxSplits) splits = kMaxSplits;
+        if (splits > K / 256) splits = K / 256;
+        *chunk = ((K + splits - 1) / splits + 31) / 32 * 32;
+        splits = (K + *chunk - 1) / *chunk;
+    }
+    return splits;
+}
+
 // Zeroes the elements of an 8-element bf16 chunk that start at index k and reach K.
 __device__ __forceinline__ uint4 mask_tail(uint4 v, int k, int K) {
     uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -84,6 +120,33 @@ __device__ __forceinline__ uint4 mask_tail(uint4 v, int k, int K) {
 // a step follow one another, as the waves of a workgroup read them.
 __host__ __device__ inline int64_t packed_elems(int ncols, int K) {
     return (int64_t)((ncols + 15) / 16) * ((K + 31) / 32) * 512;
+}
+
+// Chunk i (8 elements) of a matrix in fragment order: element (row, k) at W[row * ld + k],
+// or with TR at W[k * ld + row].
+template <bool TR>
+__device__ __forceinline__ void pack_chunk(uint16_t* __restrict__ out, const uint16_t* __restrict__ W, int rows, int K,
+                                           int ld, int64_t i) {
+    const int tiles = (rows + 15) / 16;
+    const int lane = (int)(i & 63), t = (int)((i >> 6) % tiles), kc = (int)((i >> 6) / tiles);
+    const int row = 16 * t + (lane & 15), k = 32 * kc + 8 * (lane >> 4);
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (row < rows && k < K) {
+        if constexpr (TR) {
+            uint32_t w[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t a = k + 2 * q < K ? W[(int64_t)(k + 2 * q) * ld + row] : 0u;
+                const uint32_t b = k + 2 * q + 1 < K ? W[(int64_t)(k + 2 * q + 1) * ld + row] : 0u;
+                w[q] = a | (b << 16);
+            }
+            v = make_uint4(w[0], w[1], w[2], w[3]);
+        } else {
+            v = *(const uint4*)(W + (int64_t)row * ld + k);
+            if (k + 8 > K) v = mask_tail(v, k, K);
+        }
+    }
+    ((uint4*)out)[i] = v;
 }
 
 // A workgroup is 8 waves over 16 MR rows; a wave takes every row and two column tiles at

@@ -157,6 +157,54 @@ def test_gradients(lb, orc, L, hidden, n):
     assert np.all(W1[:, lay.d_in:] == 0)
 
 
+@pytest.mark.parametrize("L,hidden,n", [(5, 64, 1), (5, 256, 33), (37, 192, 15), (53, 128, 17), (101, 256, 31),
+                                        (257, 64, 700), (639, 256, 257), (1023, 256, 16), (1023, 64, 49)])
+def test_training_pass_edges(lb, orc, L, hidden, n):
+    """The one-workgroup rows and the batch products at their edges: 16-row workgroups,
+    32-row steps, 64-column tiles, splits.  Tolerance as above; the pads of X and of
+    the parameters hold NaN.  A training step from the sequences has the same
+    gradients bit for bit, and its update is Adam of them."""
+    import torch
+    lay, P, blob, pb = _params(lb, L, hidden, 61)
+    blob = blob.cpu().numpy().copy()
+    blob[:hidden * lay.ld_in].reshape(hidden, lay.ld_in)[:, lay.d_in:] = np.nan
+    blob[lay.off_W3 + lay.d_out * hidden:lay.off_W3 + lay.ld_out * hidden] = np.nan
+    blob = torch.from_numpy(blob).cuda()
+    lb.mlp_cast(lay, blob, pb)
+    S = li.random_skew(19 * L, n, L, 0)
+    seqs = _dev_i32(li.pack(S))
+    X = lb.mlp_features(L, seqs)
+    X[:, lay.d_in:] = float("nan")
+    adm, labels, words = _mask_labels(L + 1, n, lay.d_out)
+    words_d, labels_d = _dev_i32(words), torch.from_numpy(labels).cuda()
+    G, loss = lb.mlp_grads(lay, blob, pb, X, words_d, labels_d)
+    Gd = lb.mlp_dict_from_blob(lay, G.cpu().numpy())
+    ops = {}
+    lr, Gr = omlp.loss_and_grads(P, omlp.features(S, _c_even(orc, S)), adm, labels, exact=False, operands=ops)
+    norms = omlp.term_norms(ops)
+    assert abs(float(loss.item()) - lr) <= 1e-3 * max(1.0, abs(lr))
+    for key in omlp_keys():
+        tol = 1e-2 * np.abs(Gr[key]) + 2.0 ** -7 * norms[key] + 1e-9
+        assert not (np.abs(Gd[key] - Gr[key]) > tol).any(), key
+    used = lb.mlp_blob_from_dict(lay, {key: np.ones_like(Gr[key]) for key in omlp_keys()})
+    assert np.all(G.cpu().numpy()[used == 0] == 0)
+
+    A = [torch.zeros_like(blob).copy_(torch.nan_to_num(blob)) for _ in range(2)]
+    B = [torch.empty_like(pb) for _ in range(2)]
+    for x, y in zip(A, B):
+        lb.mlp_cast(lay, x, y)
+    M = [torch.full_like(blob, 0.01) for _ in range(2)]
+    V = [torch.full_like(blob, 0.02) for _ in range(2)]
+    G1 = torch.full_like(blob, 7.0)
+    loss1, _ = lb.mlp_train_step(lay, A[0], B[0], G1, M[0], V[0], 3, seqs, words_d, labels_d)
+    G2, loss2 = lb.mlp_grads(lay, A[1], B[1], torch.nan_to_num(X), words_d, labels_d)
+    lb.mlp_adam(lay, A[1], B[1], G2, M[1], V[1], 3)
+    assert torch.equal(G1, G2) and torch.equal(G1, G)
+    assert float(loss1.item()) == float(loss2.item()) == float(loss.item())
+    for x in (A, B, M, V):
+        assert torch.equal(x[0], x[1])
+
+
 def omlp_keys():
     return ("W1", "b1", "W2", "b2", "W3", "b3")
 
