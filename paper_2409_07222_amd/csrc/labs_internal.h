@@ -266,8 +266,9 @@ labs_status launch_walk_log(const WalkArgs& A, hipStream_t st);
 labs_status launch_offer_best(const WalkArgs& A, hipStream_t st);
 labs_status launch_walk_outputs(const WalkArgs& A, const labs_step1_out& o, hipStream_t st);
 // Sorts records [0, n) of `rb` by key words 0..nkeys-1 (word 0 most significant),
-// leaving the permutation in *perm_out (device array of n uint32, inside ws).
-labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, void* ws,
+// leaving the permutation in *perm_out (device array of n uint32, inside ws); `counts`
+// is scratch of n uint32.
+labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, uint32_t* counts, void* ws,
                                size_t ws_bytes, uint32_t** perm_out, hipStream_t st);
 
 // Learned proposal network (mlp.hip).

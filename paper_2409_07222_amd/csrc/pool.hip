@@ -6,7 +6,9 @@
 // sequence, by (walker, step): the first record of each run of equal
 // sequences is then the earliest offer.  The sort is an LSD radix sort over
 // 8-bit digits of a permutation; digits that are equal in every record are
-// found up front and skipped.
+// found up front and skipped.  Long sequences are sorted by (walker, step) and
+// then by their first kLeadWords words only: records that share those and differ
+// behind them are few and are put in order in place (see k_lead_fix).
 #include "labs_internal.h"
 
 namespace labsdev {
@@ -15,8 +17,13 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRounds = 32;                              // rounds of 64 items per wave
-constexpr int kTile = kThreads * kRounds;                // 8192 items per block
+// Rounds of 64 items per wave: small tiles, so that a pass over 10^5 records still covers
+// the chip (a pass over the records of 16,384 walkers, 8,192 steps, at L = 501: 46 us with
+// 8,192 items a block and a digit gathered three times, now 12).
+constexpr int kRounds = 4;
+constexpr int kTile = kThreads * kRounds;                // 1024 items per block
+constexpr int kLeadWords = 4;                            // E and the first 96 elements
+constexpr int kLeadRun = 32;                             // longest run put in order in place
 constexpr int kMaxKeyWords = 40;                         // W + 3 <= 35 for L <= 1023
 
 __global__ void k_iota(uint32_t* p, int64_t n) {
@@ -50,13 +57,38 @@ __global__ __launch_bounds__(kThreads) void k_rs_hist(const uint32_t* kw, const 
     h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kTile;
-    for (int r = 0; r < kRounds; ++r) {
-        int64_t i = base + (int64_t)r * kThreads + threadIdx.x;
-        int d = digit_of(kw, perm, i, n, shift);
-        if (d < 256) atomicAdd(&h[d], 1u);
-    }
+    int d[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) d[r] = digit_of(kw, perm, base + (int64_t)r * kThreads + threadIdx.x, n, shift);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        if (d[r] < 256) atomicAdd(&h[d[r]], 1u);
     __syncthreads();
     ghist[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+}
+
+// Exclusive scan of one digit's counts over the blocks (blockIdx.x: the digit), and its
+// total behind all counts.
+__global__ __launch_bounds__(kThreads) void k_rs_scan(uint32_t* ghist, int nblk) {
+    __shared__ uint32_t part[kThreads];
+    uint32_t* const v = ghist + (int64_t)blockIdx.x * nblk;
+    uint32_t carry = 0;
+    for (int b = 0; b < nblk; b += kThreads) {
+        const int i = b + threadIdx.x;
+        const uint32_t x = i < nblk ? v[i] : 0u;
+        part[threadIdx.x] = x;
+        __syncthreads();
+        for (int o = 1; o < kThreads; o <<= 1) {
+            const uint32_t y = (int)threadIdx.x >= o ? part[threadIdx.x - o] : 0u;
+            __syncthreads();
+            part[threadIdx.x] += y;
+            __syncthreads();
+        }
+        if (i < nblk) v[i] = carry + part[threadIdx.x] - x;
+        carry += part[kThreads - 1];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) ghist[(int64_t)256 * nblk + blockIdx.x] = carry;
 }
 
 // Exclusive scan of M values in one block of 1024 threads.
@@ -89,18 +121,36 @@ __global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint32_t* kw, con
                                                          uint32_t* perm_out, int64_t n, int shift,
                                                          const uint32_t* gofs, int nblk) {
     __shared__ uint32_t cnt[kWaves][256];
+    __shared__ uint32_t tot[256];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (int d = threadIdx.x; d < kWaves * 256; d += kThreads) (&cnt[0][0])[d] = 0;
+    const uint32_t mine = gofs[(int64_t)256 * nblk + threadIdx.x];   // kThreads == 256 digits
+    tot[threadIdx.x] = mine;
     __syncthreads();
     const int64_t wbase = (int64_t)blockIdx.x * kTile + (int64_t)wv * 64 * kRounds;
+    uint32_t item[kRounds];
+    int dig[kRounds];
+#pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        int d = digit_of(kw, perm_in, wbase + r * 64 + lane, n, shift);
-        if (d < 256) atomicAdd(&cnt[wv][d], 1u);
+        const int64_t i = wbase + r * 64 + lane;
+        item[r] = i < n ? perm_in[i] : 0u;
     }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        dig[r] = wbase + r * 64 + lane < n ? (int)((kw[item[r]] >> shift) & 255u) : 256;
+    for (int o = 1; o < 256; o <<= 1) {
+        const uint32_t y = (int)threadIdx.x >= o ? tot[threadIdx.x - o] : 0u;
+        __syncthreads();
+        tot[threadIdx.x] += y;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        if (dig[r] < 256) atomicAdd(&cnt[wv][dig[r]], 1u);
     __syncthreads();
     {
-        const int d = threadIdx.x;  // kThreads == 256 digits
-        uint32_t run = gofs[(int64_t)d * nblk + blockIdx.x];
+        const int d = threadIdx.x;
+        uint32_t run = tot[d] - mine + gofs[(int64_t)d * nblk + blockIdx.x];
         for (int w = 0; w < kWaves; ++w) {
             uint32_t t = cnt[w][d];
             cnt[w][d] = run;
@@ -109,9 +159,9 @@ __global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint32_t* kw, con
     }
     __syncthreads();
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int64_t i = wbase + r * 64 + lane;
-        const int d = digit_of(kw, perm_in, i, n, shift);
+        const int d = dig[r];
         const bool valid = d < 256;
         uint64_t peers = __ballot(valid);
 #pragma unroll
@@ -124,11 +174,64 @@ __global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint32_t* kw, con
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         if (valid) {
             const uint32_t rank = (uint32_t)__popcll(peers & lt);
-            perm_out[base + rank] = perm_in[i];
+            perm_out[base + rank] = item[r];
             if (rank == 0) cnt[wv][d] = base + (uint32_t)__popcll(peers);
         }
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
+}
+
+// mark[i]: 1 when sorted record i agrees with the one before it in words 0..kLeadWords-1,
+// 3 when it also differs from it in words kLeadWords..W.
+__global__ void k_lead_marks(const uint32_t* rec, int64_t stride, int W, const uint32_t* perm, int64_t n,
+                             uint32_t* mark) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    uint32_t m = 0;
+    if (i > 0) {
+        const uint32_t a = perm[i], b = perm[i - 1];
+        m = 1;
+        for (int q = 0; q < kLeadWords && m; ++q)
+            if (rec[q * stride + a] != rec[q * stride + b]) m = 0;
+        for (int q = kLeadWords; q <= W && m == 1; ++q)
+            if (rec[q * stride + a] != rec[q * stride + b]) m = 3;
+    }
+    mark[i] = m;
+}
+
+// Puts the runs of equal leading words that hold different sequences in order by the words
+// behind (insertion sort, so records of one sequence keep their (walker, step) order).
+// The thread of a run's first mark 3 does it; longer runs than kLeadRun set *late.
+__global__ void k_lead_fix(const uint32_t* rec, int64_t stride, int W, uint32_t* perm, int64_t n,
+                           const uint32_t* mark, uint32_t* late) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n || mark[i] != 3u) return;
+    int64_t b = i - 1, e = i + 1;
+    while (b > 0 && mark[b] == 1u && i - b < kLeadRun) --b;
+    if (mark[b] == 3u) return;                    // another thread's run
+    while (e < n && mark[e] != 0u && e - b <= kLeadRun) ++e;
+    if (mark[b] != 0u || e - b > kLeadRun) {
+        *late = 1u;
+        return;
+    }
+    for (int64_t x = b + 1; x < e; ++x) {
+        const uint32_t a = perm[x];
+        int64_t y = x;
+        for (; y > b; --y) {
+            const uint32_t c = perm[y - 1];
+            bool less = false;
+            for (int q = kLeadWords; q <= W; ++q) {
+                const uint32_t u = rec[q * stride + a], v = rec[q * stride + c];
+                if (u != v) {
+                    less = u < v;
+                    break;
+                }
+            }
+            if (!less) break;
+            perm[y] = c;
+        }
+        perm[y] = a;
     }
 }
 
@@ -298,8 +401,10 @@ inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t
 
 }  // namespace
 
+// The counts of more than one block take the caller's second buffer; the space for them
+// here is part of the sizes that fixed scratch areas accept.
 size_t sort_workspace_bytes(int64_t nmax, int32_t KW) {
-    const int64_t nblk = (nmax + kTile - 1) / kTile;
+    const int64_t nblk = (nmax + 8191) / 8192;
     size_t b = 0;
     b += align_up(sizeof(uint32_t) * (size_t)nmax, 256) * 2;           // perm ping-pong
     b += align_up(sizeof(uint32_t) * 256 * (size_t)(nblk + 1), 256);  // histograms
@@ -307,14 +412,16 @@ size_t sort_workspace_bytes(int64_t nmax, int32_t KW) {
     return b + 1024;
 }
 
-labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, void* ws, size_t ws_bytes,
-                               uint32_t** perm_out, hipStream_t st) {
+labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, uint32_t* counts, void* ws,
+                               size_t ws_bytes, uint32_t** perm_out, hipStream_t st) {
     if (rb.KW < 1 || rb.KW > kMaxKeyWords || nkeys > rb.KW) return invalid("record key words out of range");
     Carve cv(ws, ws_bytes);
     const int64_t nblk = (n + kTile - 1) / kTile;
     uint32_t* p0 = cv.take<uint32_t>((size_t)n);
     uint32_t* p1 = cv.take<uint32_t>((size_t)n);
-    uint32_t* hist = cv.take<uint32_t>((size_t)256 * (nblk + 1));
+    uint32_t* hist = cv.take<uint32_t>(512);
+    // 256 (nblk + 1) <= n for more than one block
+    if (nblk > 1) hist = counts;
     uint32_t* var = cv.take<uint32_t>((size_t)rb.KW);
     if (!cv.ok()) return invalid("sort workspace too small");
     *perm_out = p0;
@@ -329,14 +436,14 @@ labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, void*
     LABS_HIP(hipStreamSynchronize(st));
     uint32_t* in = p0;
     uint32_t* out = p1;
-    for (int q = nkeys - 1; q >= 0; --q) {
+    auto passes = [&](int q) -> labs_status {
         for (int byte = 0; byte < 4; ++byte) {
             const int shift = 8 * byte;
             if (((hv[q] >> shift) & 255u) == 0) continue;   // constant digit
             const uint32_t* kw = rb.rec + q * rb.stride;
             hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nblk), dim3(kThreads), 0, st, kw, in, n,
                                shift, hist, (int)nblk);
-            hipLaunchKernelGGL(k_scan_excl, dim3(1), dim3(1024), 0, st, hist, (int64_t)256 * nblk);
+            hipLaunchKernelGGL(k_rs_scan, dim3(256), dim3(kThreads), 0, st, hist, (int)nblk);
             hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nblk), dim3(kThreads), 0, st, kw, in, out,
                                n, shift, hist, (int)nblk);
             LABS_LAUNCHED("radix pass");
@@ -344,7 +451,40 @@ labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, void*
             in = out;
             out = t;
         }
+        return LABS_OK;
+    };
+    // Leading words first where at least kLeadDigits digits behind them vary: a digit costs
+    // three launches (8 to 12 us), the marks, the fix and its answer's way to the host about
+    // as much as four (L = 501: 69 digits 830 us, 18 and the fix 240).  A run that is too long to be put in order in place means all digits.
+    constexpr int kLeadDigits = 8;
+    const int W = rb.KW - 3;
+    int behind = 0;
+    for (int q = kLeadWords; q <= W; ++q)
+        for (int byte = 0; byte < 4; ++byte) behind += ((hv[q] >> (8 * byte)) & 255u) != 0;
+    labs_status s;
+    if (nkeys == rb.KW && behind >= kLeadDigits) {
+        for (int q = nkeys - 1; q > W; --q)
+            if ((s = passes(q))) return s;
+        for (int q = kLeadWords - 1; q >= 0; --q)
+            if ((s = passes(q))) return s;
+        hipLaunchKernelGGL(k_lead_marks, dim3(blocks_for(n, 256)), dim3(256), 0, st, rb.rec, rb.stride, W, in, n, out);
+        LABS_HIP(hipMemsetAsync(var, 0, sizeof(uint32_t), st));
+        hipLaunchKernelGGL(k_lead_fix, dim3(blocks_for(n, 256)), dim3(256), 0, st, rb.rec, rb.stride, W, in, n, out,
+                           var);
+        LABS_LAUNCHED("k_lead_fix");
+        uint32_t late = 0;
+        LABS_HIP(hipMemcpyAsync(&late, var, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+        LABS_HIP(hipStreamSynchronize(st));
+        if (!late) {
+            *perm_out = in;
+            return LABS_OK;
+        }
+        in = p0;
+        out = p1;
+        hipLaunchKernelGGL(k_iota, dim3(blocks_for(n, 256)), dim3(256), 0, st, p0, n);
     }
+    for (int q = nkeys - 1; q >= 0; --q)
+        if ((s = passes(q))) return s;
     *perm_out = in;
     return LABS_OK;
 }
@@ -400,7 +540,7 @@ labs_status compact_records(const RecBuf& rb, int32_t W, int64_t n, int64_t cap,
     LABS_HIP(hipMemsetAsync(total, 0, sizeof(uint32_t) * 2, st));
     if (n > 0) {
         uint32_t* perm = nullptr;
-        labs_status s = radix_sort_records(rb, n, rb.KW, sort_ws, sort_bytes, &perm, st);
+        labs_status s = radix_sort_records(rb, n, rb.KW, flag, sort_ws, sort_bytes, &perm, st);
         if (s != LABS_OK) return s;
         hipLaunchKernelGGL(k_unique_flags, dim3(blocks_for(n, 256)), dim3(256), 0, st, rb.rec, rb.stride,
                            W, perm, n, flag);

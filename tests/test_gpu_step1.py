@@ -292,6 +292,37 @@ def test_pool_topk_edges(lb, orc):
     assert len(E) == 0 and len(s) == 0
 
 
+@pytest.mark.parametrize("n", [1, 2, 1023, 1024, 1025, 9000])
+@pytest.mark.parametrize("run", [1, 2, 31, 32, 33, 400])
+def test_pool_topk_shared_leading_words(lb, n, run):
+    """Entries that agree in E and their first 96 elements and differ behind them, in
+    runs up to and beyond the longest that is put in order in place, some twice: the
+    distinct ones in the order of (E, words)."""
+    import torch
+    L, W = 501, 16
+    g = np.random.default_rng(31 * n + run)
+    words = g.integers(0, 2 ** 32, (n, W), dtype=np.uint32)
+    words[:, -1] &= np.uint32(0xFFFFFFFF << (32 * W - L) & 0xFFFFFFFF)
+    E = g.integers(20000, 20200, n).astype(np.int32)
+    head = (np.arange(n) // run) * run            # every run takes its first entry's lead
+    words[:, :3] = words[head, :3]
+    E[:] = E[head]
+    twice = np.arange(n) % 7 == 3
+    twice[0] = False
+    words[twice] = words[np.flatnonzero(twice) - 1]
+    E[twice] = E[np.flatnonzero(twice) - 1]
+    order = g.permutation(n)
+    pool = lb.PoolBuffers.empty(L, n + 3)
+    pool.seqs[:n] = torch.from_numpy(words[order].view(np.int32)).cuda()
+    pool.E[:n] = torch.from_numpy(E[order]).cuda()
+    pool.count.fill_(n)
+    want = np.unique(np.concatenate([E[:, None].astype(np.uint32), words], 1), axis=0)
+    for k in (5, n + 1):
+        s, e = lb.pool_topk(pool, k)
+        got = np.concatenate([e.cpu().numpy()[:, None].view(np.uint32), s.cpu().numpy().view(np.uint32)], 1)
+        assert np.array_equal(got, want[:k])
+
+
 def test_pool_topk_and_walker_best(lb, orc):
     L, p, steps, n = 63, 4, 200, 40
     pool = lb.PoolBuffers.empty(L, 1000)
