@@ -263,6 +263,9 @@ labs_status autotune_get(int L, int p, int* rb, int* waves);
 labs_status launch_walk(const WalkArgs& A, hipStream_t st);
 // The plain walk with the learned walk's outputs (moves, hit, evals, training log).
 labs_status launch_walk_log(const WalkArgs& A, hipStream_t st);
+// Short sequences, several walkers a wave (walk_group.hip).
+int walk_group(int L, int p, int64_t n);
+labs_status launch_walk_group(const WalkArgs& A, int G, hipStream_t st);
 labs_status launch_offer_best(const WalkArgs& A, hipStream_t st);
 labs_status launch_walk_outputs(const WalkArgs& A, const labs_step1_out& o, hipStream_t st);
 // Sorts records [0, n) of `rb` by key words 0..nkeys-1 (word 0 most significant),

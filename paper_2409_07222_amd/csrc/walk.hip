@@ -250,6 +250,8 @@ labs_status launch_walk(const WalkArgs& A, hipStream_t st) {
         LABS_LAUNCHED("k_walk_bloom");
         return LABS_OK;
     }
+    const int group = walk_group(A.L, A.p, A.n);
+    if (group > 1) return launch_walk_group(A, group, st);
     hipLaunchKernelGGL(wk.plain, dim3((unsigned)A.n), dim3(64), 0, st, A);
     LABS_LAUNCHED("k_walk");
     return LABS_OK;

@@ -336,6 +336,37 @@ def test_pool_topk_and_walker_best(lb, orc):
     assert [orc.seq_key(x) for x in _host_seqs(s, L)] == [k for _, k in ref[:10]]
 
 
+@pytest.mark.parametrize("L,p,n", [(5, 0, 4097), (37, 0, 4098), (101, 8, 4099), (105, 1, 4096), (107, 8, 8193),
+                                   (125, 0, 8194), (127, 0, 8193), (127, 3, 8195), (129, 8, 8192), (201, 16, 8193),
+                                   (231, 0, 8192), (233, 16, 8193)])
+def test_several_walkers_a_wave_equal_one(lb, L, p, n):
+    """Short sequences walk four or two to a wave where there are many walkers: energies,
+    final and best states against the logging walk (a wave a walker), at the lengths where
+    the lags, the indices or a class row stop to fit, with a last wave that is not full."""
+    nf = (L - 1) // 2 + 1 - p
+    steps, lo, hi = 90, max(1, nf // 8), max(1, nf // 3)
+    a = lb.walk_step1(L, p, steps, lo, hi, 23, n, want_traj=True)
+    b = lb.learned_walk(L, p, steps, lo, hi, 23, n, mode=lb.PROPOSE_RANDOM, top_m=1, fallback_every=1, want_traj=True)
+    for key in ("traj_E", "final_seqs", "final_E", "best_seqs", "best_E", "best_step"):
+        assert np.array_equal(getattr(a, key).cpu().numpy(), b[key].cpu().numpy()), key
+
+
+@pytest.mark.parametrize("L,p", [(101, 8), (201, 12)])
+def test_several_walkers_a_wave_fill_the_same_pool(lb, L, p):
+    """The sieve of 8,192 walkers in one launch (several a wave) against four launches of
+    2,048 (a wave a walker) into one pool."""
+    lo, hi, steps, e_max = L // 10, L // 5, 150, L * L // 9
+    one, four = lb.PoolBuffers.empty(L, 1 << 18), lb.PoolBuffers.empty(L, 1 << 18)
+    lb.walk_step1(L, p, steps, lo, hi, 3, 8192, e_max=e_max, pool=one)
+    for q in range(4):
+        lb.walk_step1(L, p, steps, lo, hi, 3, 2048, walker_begin=2048 * q, e_max=e_max, pool=four)
+    c = int(one.count.item())
+    assert c > 100 and c == int(four.count.item())
+    assert int(one.dropped.item()) == int(four.dropped.item()) == 0
+    for key in ("E", "seqs", "walker", "step"):
+        assert np.array_equal(getattr(one, key)[:c].cpu().numpy(), getattr(four, key)[:c].cpu().numpy()), key
+
+
 # ------------------------------------------------------------------ edges of the walk kernel
 # Lengths on both sides of every size the matrix-core scan is instantiated at: the class
 # rows grow by 32 indices where k + 12 passes a multiple of 32 (L = 105/107, 169/171, ...,
