@@ -231,7 +231,6 @@ struct Params {
     int32_t Tr, R2;
     unsigned long long* rkey;   // [B*R2] their Zobrist keys
     int32_t* rE;                // [B*R2] their energies
-    uint32_t* pw0;              // [B] first packed word of each pivot of the round
 };
 
 __device__ __forceinline__ uint64_t zob(int i) { return zobrist_at(i); }
@@ -366,7 +365,7 @@ __device__ __forceinline__ uint32_t read32(const uint32_t* p, int W, int a) {
 // Word w of the left rotation by r (0 < r < L) of a packed sequence: element i
 // is element (i + r) mod L of the original; bits past element L-1 are 0.
 __device__ __forceinline__ uint32_t rot_word(const uint32_t* p, int L, int W, int r, int w) {
-    const int a = (32 * w + r) % L;
+    const int a = 32 * w + r < L ? 32 * w + r : 32 * w + r - L;   // 32 w < L
     const int n1 = L - a;   // elements before the wrap
     uint32_t x = read32(p, W, a);
     if (n1 < 32) x = (x & (~0u << (32 - n1))) | (read32(p, W, 0) >> n1);
@@ -1936,83 +1935,87 @@ constexpr int kMaxTr = 32;
 // pivot is computed once; moving the first element x_1 of a sequence to its end
 // changes C_k by x_1 (x_{L+1-k} - x_{1+k}), moving the last element x_L to its
 // front by x_L (x_k - x_{L-k}), so each rotation costs O(L) after the previous
-// one.  Keys are the Zobrist XOR of the rotated sequence.
+// one.  Keys are the Zobrist XOR of the rotated sequence.  A thread keeps C and the
+// Zobrist words of its lags and positions in registers, and both directions go
+// through a step together (two barriers a step).  Bound by the popcounts and that
+// chain: with the words rehashed and every index reduced by a division a rotation,
+// 1,024 pivots at L = 500, T_r = 4, 21 us, now 11.
+constexpr int kRotItems = (kMaxL + kRotThreads - 1) / kRotThreads;   // lags a thread
 __global__ __launch_bounds__(kRotThreads) void k_rot_build(Params P) {
     Ctl* c = P.ctl;
     if (c->stop) return;
     const long long b = blockIdx.x;
     if (b >= c->n_piv) return;
-    __shared__ int8_t s[kMaxL];
-    __shared__ int32_t C0[kMaxL], C[kMaxL];
-    __shared__ uint32_t V[40];
-    __shared__ int32_t red_e[kRotThreads / 64];
-    __shared__ uint32_t red_lo[kRotThreads / 64], red_hi[kRotThreads / 64];
+    __shared__ int8_t s[2 * kMaxL];               // the pivot twice over: no index wraps
+    __shared__ uint32_t V[kMaxL / 32 + 3];
+    __shared__ int32_t red_e[2][kRotThreads / 64];
+    __shared__ uint32_t red_lo[2][kRotThreads / 64], red_hi[2][kRotThreads / 64];
     const int L = P.L, W = P.W, t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const uint32_t* ps = P.H.seq + (size_t)P.piv[b] * W;
-    for (int x = t; x < L; x += kRotThreads) s[x] = ((ps[x >> 5] >> (31 - (x & 31))) & 1u) ? 1 : -1;
-    // V bit j = digit of element j (LSB first), zero past the sequence
-    for (int w = t; w < 40; w += kRotThreads) V[w] = w < W ? __builtin_bitreverse32(ps[w]) : 0u;
-    if (t == 0) P.pw0[b] = ps[0];
+    if (t < kMaxL / 32 + 3) V[t] = t < W ? ps[t] : 0u;
     __syncthreads();
-    // C_k = (L - k) - 2 (number of positions where s_i != s_{i+k}), by popcounts
-    for (int k = 1 + t; k < L; k += kRotThreads) {
-        const int q = k >> 5, r = k & 31, n = L - k;
-        int dis = 0;
-        for (int w = 0; w * 32 < n; ++w) {
-            const uint32_t sh = __builtin_amdgcn_alignbit(V[w + q + 1], V[w + q], r);
-            const int left = n - 32 * w;
-            const uint32_t m = left >= 32 ? 0xffffffffu : ((1u << left) - 1u);
-            dis += __popc((V[w] ^ sh) & m);
-        }
-        C0[k] = n - 2 * dis;
+    for (int x = t; x < L; x += kRotThreads)
+        s[x] = s[x + L] = packed_bit(V, x + 1) ? 1 : -1;
+    int32_t Cf[kRotItems], Cb[kRotItems];
+    unsigned long long z[kRotItems];
+#pragma unroll
+    for (int u = 0; u < kRotItems; ++u) {
+        const int k = 1 + t + u * kRotThreads;
+        Cf[u] = Cb[u] = k < L ? packed_corr(V, L, k) : 0;
+        z[u] = k <= L ? zob(k - 1) : 0ull;        // position k - 1
     }
     __syncthreads();
-    for (int dir = 0; dir < 2; ++dir) {
-        for (int k = 1 + t; k < L; k += kRotThreads) C[k] = C0[k];
-        __syncthreads();
-        for (int r = 1; r <= P.Tr; ++r) {
-            // x_i (1-based) of the pivot rotated by r-1 in this direction is
-            // s[(i - 1 + off) mod L]
-            const int off = dir == 0 ? r - 1 : L - (r - 1);
-            for (int k = 1 + t; k < L; k += kRotThreads) {
-                if (dir == 0)
-                    C[k] += s[off % L] * (s[(L + off - k) % L] - s[(k + off) % L]);
-                else
-                    C[k] += s[(L - 1 + off) % L] * (s[(k - 1 + off) % L] - s[(L - k - 1 + off) % L]);
+    for (int r = 1; r <= P.Tr; ++r) {
+        // element i (from 0) of the pivot rotated by r is s[i + r] forward, s[i + L - r]
+        // backward; the lags change by the elements of the rotation before this one
+        const int xf = s[r - 1], xg = s[L - r];
+        int ef = 0, eg = 0;
+        unsigned long long hf = 0, hg = 0;
+#pragma unroll
+        for (int u = 0; u < kRotItems; ++u) {
+            const int k = 1 + t + u * kRotThreads;
+            if (k < L) {
+                Cf[u] += xf * (s[L + r - 1 - k] - s[r - 1 + k]);
+                Cb[u] += xg * (s[L - r + k] - s[2 * L - r - k]);
+                ef += Cf[u] * Cf[u];
+                eg += Cb[u] * Cb[u];
             }
-            __syncthreads();
-            const int off2 = dir == 0 ? r : L - r;   // the rotation by r
-            int e = 0;
-            for (int k = 1 + t; k < L; k += kRotThreads) e += C[k] * C[k];
-            unsigned long long h = 0;
-            for (int i = t; i < L; i += kRotThreads)
-                if (s[(i + off2) % L] > 0) h ^= zob(i);
-            e = __ockl_wfred_add_i32(e);
-            uint32_t lo = (uint32_t)h, hi = (uint32_t)(h >> 32);
-            for (int o = 32; o > 0; o >>= 1) {
-                lo ^= (uint32_t)__shfl_xor((int)lo, o, 64);
-                hi ^= (uint32_t)__shfl_xor((int)hi, o, 64);
+            if (k <= L) {
+                if (s[k - 1 + r] > 0) hf ^= z[u];
+                if (s[k - 1 + L - r] > 0) hg ^= z[u];
             }
-            if (lane == 0) {
-                red_e[wv] = e;
-                red_lo[wv] = lo;
-                red_hi[wv] = hi;
-            }
-            __syncthreads();
-            if (t == 0) {
-                int E = 0;
-                uint32_t l2 = 0, h2 = 0;
-                for (int q = 0; q < kRotThreads / 64; ++q) {
-                    E += red_e[q];
-                    l2 ^= red_lo[q];
-                    h2 ^= red_hi[q];
-                }
-                const long long idx = b * P.R2 + dir * P.Tr + (r - 1);
-                P.rkey[idx] = (((unsigned long long)h2 << 32) | l2) | 1ull;
-                P.rE[idx] = E;
-            }
-            __syncthreads();
         }
+        ef = __ockl_wfred_add_i32(ef);
+        eg = __ockl_wfred_add_i32(eg);
+        uint32_t l0 = (uint32_t)hf, h0 = (uint32_t)(hf >> 32), l1 = (uint32_t)hg, h1 = (uint32_t)(hg >> 32);
+        for (int o = 32; o > 0; o >>= 1) {
+            l0 ^= (uint32_t)__shfl_xor((int)l0, o, 64);
+            h0 ^= (uint32_t)__shfl_xor((int)h0, o, 64);
+            l1 ^= (uint32_t)__shfl_xor((int)l1, o, 64);
+            h1 ^= (uint32_t)__shfl_xor((int)h1, o, 64);
+        }
+        if (lane == 0) {
+            red_e[0][wv] = ef;
+            red_lo[0][wv] = l0;
+            red_hi[0][wv] = h0;
+            red_e[1][wv] = eg;
+            red_lo[1][wv] = l1;
+            red_hi[1][wv] = h1;
+        }
+        __syncthreads();
+        if (t < 2) {
+            int E = 0;
+            uint32_t l2 = 0, h2 = 0;
+            for (int q = 0; q < kRotThreads / 64; ++q) {
+                E += red_e[t][q];
+                l2 ^= red_lo[t][q];
+                h2 ^= red_hi[t][q];
+            }
+            const long long idx = b * P.R2 + t * P.Tr + (r - 1);
+            P.rkey[idx] = (((unsigned long long)h2 << 32) | l2) | 1ull;
+            P.rE[idx] = E;
+        }
+        __syncthreads();
     }
 }
 
@@ -2020,7 +2023,13 @@ __global__ __launch_bounds__(kRotThreads) void k_rot_build(Params P) {
 // equals an earlier rotation of the round (in (pivot, q) order), when it lies
 // within one flip of a pivot of the round (it is then that pivot, CLOSED, or one
 // of the round's single-flip neighbours, which come first), or when H holds it
-// as OPEN or CLOSED; otherwise it is a new entry.  H is only read.
+// as OPEN or CLOSED; otherwise it is a new entry.  H is only read.  Bound by the latency
+// of its loads: with the round's keys loaded one a thread after the other and the
+// sequences compared word after word by one thread, 1,024 pivots at L = 500, T_r = 4,
+// 60 us, now 22.
+constexpr int kRotAhead = 8;
+constexpr int kRotBits = 1 << 15;        // of a bitmap of the Zobrist words
+constexpr int kRotNear = kRotThreads;    // pivots near a rotation that are compared together
 __global__ __launch_bounds__(kRotThreads) void k_rot_stage(Params P) {
     Ctl* c = P.ctl;
     if (c->stop) return;
@@ -2029,8 +2038,11 @@ __global__ __launch_bounds__(kRotThreads) void k_rot_stage(Params P) {
     if (b >= np) return;
     __shared__ uint32_t rw[2 * kMaxTr][32];
     __shared__ unsigned long long rk[2 * kMaxTr];
-    __shared__ int dupq[2 * kMaxTr];
-    __shared__ int s_cnt, s_min, s_max;
+    __shared__ int dupq[2 * kMaxTr], first[2 * kMaxTr], first_differs[2 * kMaxTr];
+    __shared__ uint32_t zbits[2][kRotBits / 32];
+    __shared__ int2 near[kRotNear];
+    __shared__ int near_d[kRotNear];
+    __shared__ int s_near, s_cnt, s_min, s_max;
     const int t = threadIdx.x, L = P.L, W = P.W, R2 = P.R2;
     const uint32_t last_mask = (L & 31) ? ~0u << (32 - (L & 31)) : ~0u;
     const uint32_t* ps = P.H.seq + (size_t)P.piv[b] * W;
@@ -2038,42 +2050,112 @@ __global__ __launch_bounds__(kRotThreads) void k_rot_stage(Params P) {
     if (t < R2) {
         rk[t] = P.rkey[b * R2 + t];
         dupq[t] = 0;
+        first[t] = INT32_MAX;
+        first_differs[t] = 0;
+    }
+    near_d[t] = 0;
+    for (int x = t; x < 2 * kRotBits / 32; x += kRotThreads) (&zbits[0][0])[x] = 0u;
+    __syncthreads();
+    for (int i = t; i < L; i += kRotThreads) {
+        const unsigned long long z = zob(i);
+        const uint32_t i0 = (uint32_t)(z >> 20) & (kRotBits - 1), i1 = (uint32_t)(z >> 40) & (kRotBits - 1);
+        atomicOr(&zbits[0][i0 >> 5], 1u << (i0 & 31));
+        atomicOr(&zbits[1][i1 >> 5], 1u << (i1 & 31));
     }
     if (t == 0) {
+        s_near = 0;
         s_cnt = 0;
         s_min = INT32_MAX;
         s_max = 0;
     }
     __syncthreads();
-    // earlier rotations with an equal key: compare the sequences
-    for (long long u = t; u < (b + 1) * R2; u += kRotThreads) {
-        const unsigned long long ku = P.rkey[u];
-        for (int q = 0; q < R2; ++q) {
-            if (u >= b * R2 + q || ku != rk[q]) continue;
-            const uint32_t* pu = P.H.seq + (size_t)P.piv[u / R2] * W;
-            const int su = rot_shift(P, (int)(u % R2));
-            bool eq = true;
-            for (int w = 0; w < W && eq; ++w) eq = rot_word(pu, L, W, su, w) == rw[q][w];
-            if (eq) dupq[q] = 1;
+    // Earlier rotations with an equal key: the first one of each rotation.  kRotAhead keys a
+    // thread are loaded together; the low words, eight rotations at a time, sort almost all
+    // out.
+    const long long ue = (b + 1) * R2;
+    for (long long u0 = t; u0 < ue; u0 += kRotAhead * kRotThreads) {
+        unsigned long long ku[kRotAhead];
+#pragma unroll
+        for (int a = 0; a < kRotAhead; ++a) {
+            const long long u = u0 + a * kRotThreads;
+            ku[a] = u < ue ? P.rkey[u] : 0ull;    // no key is 0
         }
-    }
-    // within one flip of a pivot of the round (first words compared first)
-    for (long long v = t; v < np; v += kRotThreads) {
-        const uint32_t w0 = P.pw0[v];
-        for (int q = 0; q < R2; ++q) {
-            uint32_t x0 = rw[q][0] ^ w0;
-            if (W == 1) x0 &= last_mask;
-            if (__popc(x0) > 1) continue;
-            const uint32_t* pv = P.H.seq + (size_t)P.piv[v] * W;
-            int d = __popc(x0);
-            for (int w = 1; w < W && d <= 1; ++w) {
-                uint32_t x = rw[q][w] ^ pv[w];
-                if (w == W - 1) x &= last_mask;
-                d += __popc(x);
+        for (int q0 = 0; q0 < R2; q0 += 8) {
+            uint32_t lo[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) lo[q] = q0 + q < R2 ? (uint32_t)rk[q0 + q] : 0u;
+#pragma unroll
+            for (int a = 0; a < kRotAhead; ++a) {
+                bool any = false;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) any |= (uint32_t)ku[a] == lo[q];
+                if (!any) continue;
+                const long long u = u0 + a * kRotThreads;
+                for (int q = q0; q < R2 && q < q0 + 8; ++q)
+                    if (u < b * R2 + q && ku[a] == rk[q]) atomicMin(&first[q], (int)u);
             }
-            if (d <= 1) dupq[q] = 1;
         }
     }
+    // Pivots of the round within one flip of a rotation: the keys then differ by nothing or
+    // one position's Zobrist word (bit 0 of a key is always set), and two bitmaps of those
+    // words' bits let one other pair in 4,000 through.
+    for (long long v = t; v < np; v += kRotThreads) {
+        const unsigned long long kv = P.pivK[v];
+        for (int q = 0; q < R2; ++q) {
+            const unsigned long long d = rk[q] ^ kv;
+            const uint32_t i0 = (uint32_t)(d >> 20) & (kRotBits - 1), i1 = (uint32_t)(d >> 40) & (kRotBits - 1);
+            if (d > 1 && !((zbits[0][i0 >> 5] >> (i0 & 31)) & (zbits[1][i1 >> 5] >> (i1 & 31)) & 1u)) continue;
+            const int at = atomicAdd(&s_near, 1);
+            if (at < kRotNear) near[at] = make_int2(q, (int)v);
+        }
+    }
+    __syncthreads();
+    // Both compared word by word, a thread a word: a round's pivots are often rotations
+    // of each other, so most rotations have such a partner.
+    const int n_near = min(s_near, kRotNear);
+    for (int x = t; x < R2 * W; x += kRotThreads) {
+        const int q = x / W, w = x - q * W, u = first[q];
+        if (u == INT32_MAX) continue;
+        const uint32_t* pu = P.H.seq + (size_t)P.piv[u / R2] * W;
+        if (rot_word(pu, L, W, rot_shift(P, u % R2), w) != rw[q][w]) first_differs[q] = 1;
+    }
+    for (int x = t; x < n_near * W; x += kRotThreads) {
+        const int i = x / W, w = x - i * W;
+        const uint32_t* pv = P.H.seq + (size_t)P.piv[near[i].y] * W;
+        uint32_t d = rw[near[i].x][w] ^ pv[w];
+        if (w == W - 1) d &= last_mask;
+        if (d) atomicAdd(&near_d[i], __popc(d));
+    }
+    __syncthreads();
+    if (t < n_near && near_d[t] <= 1) dupq[near[t].x] = 1;
+    if (t < R2 && first[t] != INT32_MAX) {
+        if (!first_differs[t]) {
+            dupq[t] = 1;
+        } else {
+            // two sequences of one key: the later ones, one by one
+            for (long long u = first[t] + 1; u < b * R2 + t; ++u) {
+                if (P.rkey[u] != rk[t]) continue;
+                const uint32_t* pu = P.H.seq + (size_t)P.piv[u / R2] * W;
+                const int su = rot_shift(P, (int)(u % R2));
+                bool eq = true;
+                for (int w = 0; w < W && eq; ++w) eq = rot_word(pu, L, W, su, w) == rw[t][w];
+                if (eq) dupq[t] = 1;
+            }
+        }
+    }
+    // more pivots near than the list holds: all of them, one by one
+    if (s_near > kRotNear)
+        for (long long v = t; v < np; v += kRotThreads)
+            for (int q = 0; q < R2; ++q) {
+                const uint32_t* pv = P.H.seq + (size_t)P.piv[v] * W;
+                int d = 0;
+                for (int w = 0; w < W && d <= 1; ++w) {
+                    uint32_t x = rw[q][w] ^ pv[w];
+                    if (w == W - 1) x &= last_mask;
+                    d += __popc(x);
+                }
+                if (d <= 1) dupq[q] = 1;
+            }
     __syncthreads();
     if (t < R2) {
         const int q = t;
@@ -2587,7 +2669,6 @@ S2Layout s2_layout(const labs_step2_cfg& c, long long n_cand) {
     t += 2 * align_up(sizeof(uint32_t) * c.batch * words_of(c.L), 256);  // pseq, this round's and the next's
     t += align_up(sizeof(unsigned long long) * (2 * c.T_r * c.batch + 1), 256);   // rotation keys
     t += align_up(sizeof(int32_t) * (2 * c.T_r * c.batch + 1), 256);              // rotation energies
-    t += align_up(sizeof(uint32_t) * c.batch, 256);                                // pivots' first words
     t += align_up(sizeof(Ctl), 256);
     t += 2 * align_up(sizeof(int32_t) * lo.cap_o, 256);                // oE
     t += 2 * align_up(sizeof(int32_t) * lo.cap_o, 256);                // oS
@@ -2660,7 +2741,6 @@ labs_status step2_run(const labs_step2_cfg& cfg, long long n_cand, const uint32_
     P.R2 = 2 * cfg.T_r;
     P.rkey = cv.take<unsigned long long>((size_t)P.R2 * cfg.batch + 1);
     P.rE = cv.take<int32_t>((size_t)P.R2 * cfg.batch + 1);
-    P.pw0 = cv.take<uint32_t>((size_t)cfg.batch);
     int tcur = 0;
     P.H = tabs[0];
     P.ctl = cv.take<Ctl>(1);

@@ -164,6 +164,22 @@ def test_step2_rotations_parity(lb, orc, L, n, B, Q, X, T_u, T_r):
     assert g["pushes"] + g["dup_skips"] == g["expansions"] * (L + 2 * T_r)
 
 
+@pytest.mark.parametrize("L,T_r", [(31, 4), (96, 5), (300, 4)])
+def test_step2_rotations_of_near_pivots(lb, orc, L, T_r):
+    """Seeds that are rotations and single flips of one another, all pivots of one round:
+    most rotations repeat another pivot's, or lie within one flip of a pivot (more pairs
+    than are compared together at the larger lengths)."""
+    c = li.random_pm1(L, 1, L)[0]
+    cands = [np.roll(c, r) for r in range(5)]
+    for r in range(5):
+        for f in range(0, L, max(1, L // 24)):
+            x = np.roll(c, r)
+            x[f] = -x[f]
+            cands.append(x)
+    cands = np.unique(np.stack(cands), axis=0)
+    _run_both(lb, orc, L, cands, 256, 4000, 2 * len(cands), 1 << 40, T_r)
+
+
 def test_step2_rotations_periodic_pivot(lb, orc):
     """A pivot of period 3 meets itself at shift 3 and repeats its own rotations."""
     L = 9
