@@ -22,7 +22,7 @@ constexpr int kWaves = kThreads / 64;
 // 8,192 items a block and a digit gathered three times, now 12).
 constexpr int kRounds = 4;
 constexpr int kTile = kThreads * kRounds;                // 1024 items per block
-constexpr int kLeadWords = 4;                            // E and the first 96 elements
+constexpr int kLeadWords = 2;                            // E and the first 32 elements
 constexpr int kLeadRun = 32;                             // longest run put in order in place
 constexpr int kMaxKeyWords = 40;                         // W + 3 <= 35 for L <= 1023
 
@@ -455,7 +455,7 @@ labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, uint3
     };
     // Leading words first where at least kLeadDigits digits behind them vary: a digit costs
     // three launches (8 to 12 us), the marks, the fix and its answer's way to the host about
-    // as much as four (L = 501: 69 digits 830 us, 18 and the fix 240).  A run that is too long to be put in order in place means all digits.
+    // as much as four (a compaction's sort at L = 501: 69 digits 830 us, 10 and the fix 160).  A run that is too long to be put in order in place means all digits.
     constexpr int kLeadDigits = 8;
     const int W = rb.KW - 3;
     int behind = 0;

