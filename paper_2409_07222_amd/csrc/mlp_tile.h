@@ -218,7 +218,7 @@ __device__ __forceinline__ void tile_product(f32x4 (&acc)[CT][MR], const char* A
 
 // Every column of a layer for the workgroup's rows: store(col, row, bias, v) takes four
 // consecutive columns of one row and their biases.
-template <int MR, class Store>
+template <int MR, int NW = kTileWaves, class Store>
 __device__ __forceinline__ void tile_layer(const char* A, int sa, const uint16_t* __restrict__ WP,
                                            const float* __restrict__ bias, int ncols, int K, Store store) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -228,7 +228,7 @@ __device__ __forceinline__ void tile_layer(const char* A, int sa, const uint16_t
         f32x4 acc[CT][MR];
         int t[CT];
 #pragma unroll
-        for (int c = 0; c < CT; ++c) t[c] = t0 + kTileWaves * c;
+        for (int c = 0; c < CT; ++c) t[c] = t0 + NW * c;
         float bv[CT][4];
 #pragma unroll
         for (int c = 0; c < CT; ++c)
@@ -240,8 +240,8 @@ __device__ __forceinline__ void tile_layer(const char* A, int sa, const uint16_t
 #pragma unroll
             for (int r = 0; r < MR; ++r) store(16 * t[c] + 4 * (lane >> 4), 16 * r + (lane & 15), bv[c], acc[c][r]);
     };
-    for (int t0 = wave; t0 < tiles; t0 += 2 * kTileWaves) {
-        if (t0 + kTileWaves < tiles) run(std::integral_constant<int, 2>(), t0);
+    for (int t0 = wave; t0 < tiles; t0 += 2 * NW) {
+        if (t0 + NW < tiles) run(std::integral_constant<int, 2>(), t0);
         else run(std::integral_constant<int, 1>(), t0);
     }
 }

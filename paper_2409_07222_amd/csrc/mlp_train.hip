@@ -11,8 +11,8 @@
 // Every sum has the order of the separate products' path (mlp.hip), so gradients do not
 // depend on which of the two computes them.
 // As some twenty launches of products, column sums, split sums and elementwise passes the
-// step took 189 us at L = 501, hidden 256, n = 4,096; now 62 (packing
-// 5, rows 36, batch products 16, sums and Adam 9).
+// step took 189 us at L = 501, hidden 256, n = 4,096; now 56 (packing 5, rows 29, batch
+// products 16, sums and Adam 9).
 #include "labs_internal.h"
 
 #include <cmath>
@@ -24,6 +24,7 @@ namespace labsdev {
 namespace {
 
 constexpr int kRows = 16;                     // rows of a workgroup of k_train_rows
+constexpr int kRowWaves = 16, kRowThreads = 64 * kRowWaves;   // a wave a row, a column tile
 constexpr int kGradTile = 64;                 // tile edge of a weight gradient product
 
 struct TrainArgs {
@@ -87,7 +88,7 @@ __host__ __device__ inline RowsLds rows_lds(const labs_mlp_layout& y) {
 // step's fragments.
 __device__ __forceinline__ void write_columns(uint16_t* __restrict__ F, const char* A, int sa, int ncols) {
     const int tiles = (ncols + 15) >> 4, kc = blockIdx.x >> 1;
-    for (int it = threadIdx.x; it < 32 * tiles; it += kTileThreads) {
+    for (int it = threadIdx.x; it < 32 * tiles; it += kRowThreads) {
         const int t = it >> 5, l = it & 31;
         const char* a = A + 8 * (l >> 4) * sa + 2 * (16 * t + (l & 15));
         uint32_t w[4];
@@ -99,63 +100,51 @@ __device__ __forceinline__ void write_columns(uint16_t* __restrict__ F, const ch
     }
 }
 
-// A wave's two column tiles (wave, wave + 8) of a product with up to 256 columns.
-__device__ __forceinline__ void tile_two(f32x4 (&acc)[2], const char* A, int sa, const uint16_t* WP, int ncols, int K) {
+// A wave's column tile of a product with up to 256 columns.
+__device__ __forceinline__ void tile_one(f32x4& acc, const char* A, int sa, const uint16_t* WP, int ncols, int K) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tiles = ncols >> 4, nch = (K + 31) >> 5;
-    acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (wave + kTileWaves < tiles) {
-        f32x4 v[2][1];
-        const int t[2] = {wave, wave + kTileWaves};
-        tile_product<1, 2>(v, A, sa, WP, t, tiles, nch);
-        acc[0] = v[0][0];
-        acc[1] = v[1][0];
-    } else if (wave < tiles) {
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (wave < tiles) {
         f32x4 v[1][1];
         const int t[1] = {wave};
         tile_product<1, 1>(v, A, sa, WP, t, tiles, nch);
-        acc[0] = v[0][0];
+        acc = v[0][0];
     }
 }
 
 // Hidden layer: h = gelu(v + b) as bf16 into LDS, gelu'(v + b) kept in FP32 registers
 // (the backward product of the layer ends in the same lanes).
-__device__ __forceinline__ void hidden_forward(f32x4 (&grad)[2], const f32x4 (&acc)[2], const float* bias, char* H,
+__device__ __forceinline__ void hidden_forward(f32x4& grad, const f32x4& acc, const float* bias, char* H,
                                                int sh, int ncols) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = 16 * wave + 4 * (lane >> 4);
+    if (col >= ncols) return;
+    uint32_t h[4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const int col = 16 * (wave + kTileWaves * c) + 4 * (lane >> 4);
-        if (col >= ncols) continue;
-        uint32_t h[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float x = acc[c][j] + bias[col + j];
-            h[j] = f2bf(gelu_f(x));
-            grad[c][j] = gelu_grad_f(x);
-        }
-        *(uint2*)(H + (lane & 15) * sh + 2 * col) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    for (int j = 0; j < 4; ++j) {
+        const float x = acc[j] + bias[col + j];
+        h[j] = f2bf(gelu_f(x));
+        grad[j] = gelu_grad_f(x);
     }
+    *(uint2*)(H + (lane & 15) * sh + 2 * col) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
 }
 
 // d = dh gelu': FP32 rows to memory, bf16 rows into LDS.
-__device__ __forceinline__ void hidden_backward(const f32x4 (&dh)[2], const f32x4 (&grad)[2], float* D, int ldd, int rows,
+__device__ __forceinline__ void hidden_backward(const f32x4& dh, const f32x4& grad, float* D, int ldd, int rows,
                                                 char* H, int sh, int ncols) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane & 15;
+    const int col = 16 * wave + 4 * (lane >> 4);
+    if (col >= ncols) return;
+    float d[4];
+    uint32_t h[4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const int col = 16 * (wave + kTileWaves * c) + 4 * (lane >> 4);
-        if (col >= ncols) continue;
-        float d[4];
-        uint32_t h[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            d[j] = dh[c][j] * grad[c][j];
-            h[j] = f2bf(d[j]);
-        }
-        *(uint2*)(H + row * sh + 2 * col) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-        if (row < rows) *(float4*)(D + (int64_t)row * ldd + col) = make_float4(d[0], d[1], d[2], d[3]);
+    for (int j = 0; j < 4; ++j) {
+        d[j] = dh[j] * grad[j];
+        h[j] = f2bf(d[j]);
     }
+    *(uint2*)(H + row * sh + 2 * col) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    if (row < rows) *(float4*)(D + (int64_t)row * ldd + col) = make_float4(d[0], d[1], d[2], d[3]);
 }
 
 __device__ __forceinline__ float wave_max(float v) {
@@ -168,10 +157,11 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // 16 rows, so the training batch (4,096) is one workgroup a CU; bound by the latency of its
-// chain of five products with a barrier each (36 us; without the lags' popcounts, GELU or
-// the columns' writes 33 to 35, and no less with weights read 8 or 12 steps ahead).
+// chain of five products with a barrier each, so every wave takes one column tile (29 us;
+// eight waves with two tiles 36, and of those the lags' popcounts, GELU and the columns'
+// writes 1 to 3 each; weights read 8 or 12 steps ahead no less).
 template <bool SEQ>
-__global__ __launch_bounds__(kTileThreads, 4) void k_train_rows(TrainArgs T) {
+__global__ __launch_bounds__(kRowThreads) void k_train_rows(TrainArgs T) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ uint32_t sw[kRows][36];
     const labs_mlp_layout& y = T.y;
@@ -185,8 +175,8 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_train_rows(TrainArgs T) {
 
     // ---- features; rows past n repeat the last one, and have a zero dz
 #pragma unroll
-    for (int i = 0; i < kRows / kTileWaves; ++i) {
-        const int row = wave + kTileWaves * i;
+    for (int i = 0; i < kRows / kRowWaves; ++i) {
+        const int row = wave + kRowWaves * i;
         const int64_t r = min(m0 + row, T.n - 1);
         char* const x = X + row * o.sx;
         if constexpr (SEQ) {
@@ -213,16 +203,16 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_train_rows(TrainArgs T) {
     __syncthreads();
 
     // ---- forward
-    f32x4 acc[2], g1[2], g2[2];
-    tile_two(acc, X, o.sx, T.W1, y.hidden, y.d_in);
+    f32x4 acc, g1, g2;
+    tile_one(acc, X, o.sx, T.W1, y.hidden, y.d_in);
     hidden_forward(g1, acc, T.P + y.off_b1, H1, o.sh, y.hidden);
     write_columns(T.FX, X, o.sx, y.d_in);
     __syncthreads();
-    tile_two(acc, H1, o.sh, T.W2, y.hidden, y.hidden);
+    tile_one(acc, H1, o.sh, T.W2, y.hidden, y.hidden);
     hidden_forward(g2, acc, T.P + y.off_b2, H2, o.sh, y.hidden);
     write_columns(T.F1, H1, o.sh, y.hidden);
     __syncthreads();
-    tile_layer<1>(H2, o.sh, T.W3, T.P + y.off_b3, y.d_out, y.hidden,
+    tile_layer<1, kRowWaves>(H2, o.sh, T.W3, T.P + y.off_b3, y.d_out, y.hidden,
                   [&](int col, int row, const float (&b)[4], f32x4 v) {
                       *(float4*)(Z + row * o.sz + 4 * col) =
                           make_float4(v[0] + b[0], v[1] + b[1], v[2] + b[2], v[3] + b[3]);
@@ -234,8 +224,8 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_train_rows(TrainArgs T) {
     // loss = logsumexp - z_label, dz = (softmax - onehot) / n there, 0 elsewhere
     const float inv_n = 1.0f / (float)T.n;
 #pragma unroll
-    for (int i = 0; i < kRows / kTileWaves; ++i) {
-        const int row = wave + kTileWaves * i, r = m0 + row;
+    for (int i = 0; i < kRows / kRowWaves; ++i) {
+        const int row = wave + kRowWaves * i, r = m0 + row;
         const bool in = r < T.n;
         const float* const z = (const float*)(Z + row * o.sz);
         uint16_t* const dz = (uint16_t*)(DZ + row * o.sd);
@@ -274,11 +264,11 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_train_rows(TrainArgs T) {
     __syncthreads();
 
     // ---- backward
-    tile_two(acc, DZ, o.sd, T.W3T, y.hidden, y.d_out);
+    tile_one(acc, DZ, o.sd, T.W3T, y.hidden, y.d_out);
     hidden_backward(acc, g2, D + y.hidden, ldd, rows, H2, o.sh, y.hidden);
     write_columns(T.FZ, DZ, o.sd, y.d_out);
     __syncthreads();
-    tile_two(acc, H2, o.sh, T.W2T, y.hidden, y.hidden);
+    tile_one(acc, H2, o.sh, T.W2T, y.hidden, y.hidden);
     hidden_backward(acc, g1, D, ldd, rows, H1, o.sh, y.hidden);
     write_columns(T.FD2, H2, o.sh, y.hidden);
     __syncthreads();
@@ -553,10 +543,10 @@ labs_status mlp_train(const labs_mlp_layout& y, float* P, uint16_t* Pb, int64_t 
     const int lds = rows_lds(y).bytes;
     if (seqs) {
         LABS_HIP(hipFuncSetAttribute((const void*)k_train_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        hipLaunchKernelGGL(k_train_rows<true>, rows, dim3(kTileThreads), lds, st, T);
+        hipLaunchKernelGGL(k_train_rows<true>, rows, dim3(kRowThreads), lds, st, T);
     } else {
         LABS_HIP(hipFuncSetAttribute((const void*)k_train_rows<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        hipLaunchKernelGGL(k_train_rows<false>, rows, dim3(kTileThreads), lds, st, T);
+        hipLaunchKernelGGL(k_train_rows<false>, rows, dim3(kRowThreads), lds, st, T);
     }
     LABS_LAUNCHED("k_train_rows");
     const int blocks = grad_blocks(y, T.splits);
