@@ -27,8 +27,9 @@ __device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_AC
 // read of the row with the matching shift; each row ends in 16 zero bytes, and its
 // length is an odd multiple of 16 bytes so that 16 rows fall into distinct banks.
 // D holds -C_{2|t|} at db + t (0 at t = 0), low bytes; DH the bytes above them.
-// T holds the tabu deadlines of the slots, four of a lane in one 16-byte read.
-template <int KH, int NT, int NQ>
+// T holds the tabu deadlines of the slots, four of a lane in one 16-byte read (with a
+// Bloom filter there are none).
+template <int KH, int NT, int NQ, bool BL = false>
 struct Lds {
     static constexpr int ROW = 32 * KH;
     static constexpr int ST = ROW + 16;
@@ -38,7 +39,7 @@ struct Lds {
     int8_t DH[DNEG + DPOS] __attribute__((aligned(16)));
     int8_t guard[16] __attribute__((aligned(16)));        // zeros before the first row
     int8_t X[16 * ST];
-    int32_t T[256 * NT] __attribute__((aligned(16)));
+    int32_t T[BL ? 4 : 256 * NT] __attribute__((aligned(16)));
     uint32_t pk[24];
 };
 
@@ -81,8 +82,8 @@ __host__ __device__ inline int first_index(int k, int p) {
 // BL: self-avoidance by the walker's Bloom filter (copied into `bl` in LDS for the
 // segment) instead of the tabu tenure.  LG: the training log's outputs.
 template <int KH, int NT, int NQ, bool BL, bool LG>
-__device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, NT, NQ>& S, uint32_t* bl) {
-    typedef Lds<KH, NT, NQ> T;
+__device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, NT, NQ, BL>& S, uint32_t* bl) {
+    typedef Lds<KH, NT, NQ, BL> T;
     constexpr int ST = T::ST, ROW = T::ROW;
     const int lane = threadIdx.x & 63;
     const int L = A.L, k = A.k, p = A.p, W = A.W, nf = A.nf;
@@ -203,6 +204,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
     int az[NT][4];                                // a - 1 of the lane's slots
     int Y[NT][4];                                 // dE/4 without the terms in H and C
     int sgs[NT][4];                               // 1, the centre 0
+    int least[NT][4];                             // Bloom: INT_MIN, where no slot is INT_MAX
     int xso[NT], xeo[NT];
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
@@ -220,6 +222,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
             const bool valid = n >= 0 && x > p && x <= k + 1;
             const int i = x - p - 1;
             tb[r] = !valid ? INT_MAX : BL ? 0 : A.tabu[j * nf + i];
+            least[u][r] = valid ? INT_MIN : INT_MAX;
             // sum_m x[n + m] x[n - m]
             int y = 0;
             if (valid) {
@@ -241,7 +244,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
             az[u][r] = 2 * n + cl;
             asm("" : "+v"(az[u][r]));             // kept, not recomputed each step
         }
-        *(v4i*)(S.T + cl * 128 * NT + 128 * u + 8 * lj + 4 * (lg & 1)) = tb;
+        if constexpr (!BL) *(v4i*)(S.T + cl * 128 * NT + 128 * u + 8 * lj + 4 * (lg & 1)) = tb;
     }
     const int aoff = (lane & 15) * ST + 16 * lg;
     const int boff = db + 16 * lg - kz - n0 - 8 * lj;
@@ -306,7 +309,8 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
     int bestT = uni(A.bestT[j]);
     // Bloom: undoing the last move returns to a sequence the filter holds (no false
     // negatives), so the last slot is out for one step without a probe
-    const int tenure = BL ? 1 : uni(A.tenure[j]);
+    int last = -1;
+    const int tenure = BL ? 0 : uni(A.tenure[j]);
     const int thr = !LG && A.e_max >= 0 ? A.e_max : INT_MIN;   // sieve threshold
     const int64_t wid = A.walker_begin + j;
     int pend = pending_level(A);          // first-hit stamps: largest level energy above E
@@ -363,7 +367,8 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
             const int* pe = (const int*)(S.X + xeo[u]);
             const int e0 = pe[0], e1 = pe[1], e2 = pe[2];
             const int cd0 = *(const int*)(S.D + co01 + cstep * u), cd1 = *(const int*)(S.D + co23 + cstep * u);
-            const v4i tb = *(const v4i*)(S.T + toff + 128 * u);
+            v4i tb = {0, 0, 0, 0};
+            if constexpr (!BL) tb = *(const v4i*)(S.T + toff + 128 * u);
             if (wide) {
                 const v4i Hh = product(S.DH + boff - 128 * u);
                 const int ch0 = *(const int*)(S.DH + co01 + cstep * u), ch1 = *(const int*)(S.DH + co23 + cstep * u);
@@ -392,9 +397,13 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
                 int d = (labs_mul_i24(s, v[r]) << sgs[u][r]) + Y[u][r];
                 d = __builtin_amdgcn_sdot4(r < 2 ? cd0 : cd1, r & 1 ? cwB : cwA, d, false);
                 const int kk = (d << 8) + az[u][r];
-                const bool adm = tb[r] < t;
-                if constexpr (LG) ncand += __popcll(__ballot(adm));
-                key[u][r] = adm ? kk : INT_MAX;
+                if constexpr (BL) {
+                    key[u][r] = az[u][r] == last ? INT_MAX : max(kk, least[u][r]);
+                } else {
+                    const bool adm = tb[r] < t;
+                    if constexpr (LG) ncand += __popcll(__ballot(adm));
+                    key[u][r] = adm ? kk : INT_MAX;
+                }
                 if constexpr (!BL) kmin = min(kmin, key[u][r]);
             }
         }
@@ -435,6 +444,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
         E += 8 * (kmin >> 9);
         // ---- the flipped pair: class cs, indices n and nbs
         const int z = kmin & 511, n = z >> 1, cs = z & 1;
+        last = z;
         const int q = n - n0;
         const int nbs = k - n - cs;
         const bool cen = n == nbs;
@@ -475,7 +485,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& A, int64_t j, Lds<KH, 
         lds_order();
         if (lane < 16) {
             *xw = 0;
-            S.T[cs * 128 * NT + q] = t + tenure;
+            if constexpr (!BL) S.T[cs * 128 * NT + q] = t + tenure;
         }
         lds_order();
         // ---- Y: the pairs (n_f, 2 na - n_f) of each flipped index n_f change sign
@@ -613,10 +623,14 @@ __global__ __launch_bounds__(64, (WavesPerSimd<KH, NT>::value)) void k_walk(Walk
     walk_body<KH, NT, NQ, false, false>(A, blockIdx.x, S, nullptr);
 }
 
-// Bloom-filter form: the walker's filter (2^bloom_log2 bits) in dynamic LDS.
+// Bloom-filter form: the walker's filter (2^bloom_log2 bits) in dynamic LDS, which decides
+// how many walkers reside; without the tabu deadlines a walker takes 1 KB less.  Registers
+// for five waves where the plain walk has six: 16,384 walkers at L = 451, us a step at 2^12,
+// 2^13, 2^15, 2^16 bits: 5.28, 5.13, 5.93, 7.35 (six 4.99, 5.28, 6.08, 7.47; with the
+// deadlines in LDS 5.44, 5.72, 6.53, 7.95).
 template <int KH, int NT, int NQ>
-__global__ __launch_bounds__(64, (WavesPerSimd<KH, NT>::value)) void k_walk_bloom(WalkArgs A) {
-    __shared__ Lds<KH, NT, NQ> S;
+__global__ __launch_bounds__(64, (WavesPerSimd<KH, NT>::value > 5 ? 5 : WavesPerSimd<KH, NT>::value)) void k_walk_bloom(WalkArgs A) {
+    __shared__ Lds<KH, NT, NQ, true> S;
     extern __shared__ uint32_t bloom_words[];
     walk_body<KH, NT, NQ, true, false>(A, blockIdx.x, S, bloom_words);
 }
