@@ -24,15 +24,20 @@ __device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_AC
 
 // X holds, for class cl and shift i = 0..7, row cl*8 + i: byte kap is x_cl[i + kap - kz]
 // (0 outside the sequence), so any dword or 8-byte run of a class is one aligned
-// read of the row with the matching shift; each row ends in 16 zero bytes, and its
-// length is an odd multiple of 16 bytes so that 16 rows fall into distinct banks.
+// read of the row with the matching shift; each row ends in 16 zero bytes or more.  A row
+// length of 2 mod 4 units of 16 bytes keeps the 16-byte operand reads free of bank
+// conflicts (the 16 lanes served together are eight rows at one step and eight at the next;
+// at odd lengths they take twice the cycles), so rows are 32 bytes longer at even KH:
+// 16,384 walkers at L = 301 3.61 -> 3.56 us a step, L = 451 4.16 -> 4.07.  At odd KH that
+// takes 64 bytes, and the LDS costs a wave (L = 501 4.30 -> 4.59); so it does beside a
+// Bloom filter.
 // D holds -C_{2|t|} at db + t (0 at t = 0), low bytes; DH the bytes above them.
 // T holds the tabu deadlines of the slots, four of a lane in one 16-byte read (with a
 // Bloom filter there are none).
 template <int KH, int NT, int NQ, bool BL = false>
 struct Lds {
     static constexpr int ROW = 32 * KH;
-    static constexpr int ST = ROW + 16;
+    static constexpr int ST = ROW + (BL || (KH & 1) ? 16 : 32);
     static constexpr int DNEG = NQ == 1 ? 336 : 520;
     static constexpr int DPOS = (ROW > 256 * NQ ? ROW : 256 * NQ) + 32;
     int8_t D[DNEG + DPOS] __attribute__((aligned(16)));   // first: short offsets of paired reads
