@@ -661,7 +661,6 @@ __global__ __launch_bounds__(kTileThreads, MR == 4 ? 2 : 4) void k_forward(FwdAr
     });
 }
 
-constexpr int kLdsBytes = 160 * 1024;
 // Widest hidden layer of the one-workgroup kernel: beyond it two layers' rows no longer
 // leave room for a second workgroup at L = 501, and the separate products' tiles are full.
 constexpr int kFusedHidden = 256;

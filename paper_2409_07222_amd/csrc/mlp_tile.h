@@ -84,6 +84,11 @@ __device__ __forceinline__ void adam_update(int64_t i, float g, float* __restric
     Pb[i] = f2bf(p);
 }
 
+// LDS of a workgroup.  The kernels that take more than the default limit have it raised to
+// this, less their static part, and not to what a call needs: the limit is the process's,
+// so another thread's smaller network would lower it before this one's launch.
+constexpr int kLdsBytes = 160 * 1024;
+
 // Chunks of rows of a bias gradient's sum.
 constexpr int kColChunks = 64;
 

@@ -25,6 +25,7 @@ namespace {
 
 constexpr int kRows = 16;                     // rows of a workgroup of k_train_rows
 constexpr int kRowWaves = 16, kRowThreads = 64 * kRowWaves;   // a wave a row, a column tile
+constexpr int kSeqWords = 36;                 // packed words of a row with zeros behind
 constexpr int kGradTile = 64;                 // tile edge of a weight gradient product
 
 struct TrainArgs {
@@ -163,7 +164,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 template <bool SEQ>
 __global__ __launch_bounds__(kRowThreads) void k_train_rows(TrainArgs T) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    __shared__ uint32_t sw[kRows][36];
+    __shared__ uint32_t sw[kRows][kSeqWords];
     const labs_mlp_layout& y = T.y;
     const RowsLds o = rows_lds(y);
     char *const X = lds + o.x, *const H1 = lds + o.h1, *const H2 = lds + o.h2, *const Z = lds + o.z,
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(kRowThreads) void k_train_rows(TrainArgs T) {
         char* const x = X + row * o.sx;
         if constexpr (SEQ) {
             const int L = y.L, k = y.k, W = (L + 31) >> 5;
-            if (lane < 36) sw[row][lane] = lane < W ? T.seqs[r * W + lane] : 0u;
+            if (lane < kSeqWords) sw[row][lane] = lane < W ? T.seqs[r * W + lane] : 0u;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             const uint32_t* u = sw[row];
             for (int e = lane; e < k; e += 64) {
@@ -541,11 +542,13 @@ labs_status mlp_train(const labs_mlp_layout& y, float* P, uint16_t* Pb, int64_t 
     LABS_LAUNCHED("k_pack_train");
     const dim3 rows((unsigned)(2 * T.ksteps));
     const int lds = rows_lds(y).bytes;
+    constexpr int kLimit = kLdsBytes - kRows * kSeqWords * (int)sizeof(uint32_t);
     if (seqs) {
-        LABS_HIP(hipFuncSetAttribute((const void*)k_train_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        LABS_HIP(hipFuncSetAttribute((const void*)k_train_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kLimit));
         hipLaunchKernelGGL(k_train_rows<true>, rows, dim3(kRowThreads), lds, st, T);
     } else {
-        LABS_HIP(hipFuncSetAttribute((const void*)k_train_rows<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        LABS_HIP(hipFuncSetAttribute((const void*)k_train_rows<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     kLimit));
         hipLaunchKernelGGL(k_train_rows<false>, rows, dim3(kRowThreads), lds, st, T);
     }
     LABS_LAUNCHED("k_train_rows");

@@ -1,0 +1,71 @@
+"""What the library's host code asks of the HIP runtime, recorded by a stand-in for the
+runtime (hip_stub.c): no GPU, nothing is computed.  Each case runs in a process of its
+own, where the stand-in's symbols come before the runtime's."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(ROOT, "paper_2409_07222_amd", "liblabs.so")
+
+pytestmark = [pytest.mark.skipif(not os.path.exists(LIB), reason="library not built"),
+              pytest.mark.skipif(shutil.which("gcc") is None, reason="no C compiler")]
+
+PRELUDE = """
+import ctypes, os, sys
+sys.path.insert(0, %(root)r)
+S = ctypes.CDLL(%(stub)r, mode=ctypes.RTLD_GLOBAL)
+from paper_2409_07222_amd import labs
+H = labs.lib()
+class Launch(ctypes.Structure):
+    _fields_ = [("name", ctypes.c_char_p), ("grid", ctypes.c_uint32), ("block", ctypes.c_uint32),
+                ("shmem", ctypes.c_size_t)]
+class Attr(ctypes.Structure):
+    _fields_ = [("name", ctypes.c_char_p), ("attr", ctypes.c_int), ("value", ctypes.c_int)]
+def launches():
+    n = ctypes.c_int.in_dll(S, "stub_n_launches").value
+    return list((Launch * 65536).in_dll(S, "stub_launches"))[:n]
+def attrs():
+    n = ctypes.c_int.in_dll(S, "stub_n_attrs").value
+    return list((Attr * 65536).in_dll(S, "stub_attrs"))[:n]
+P = 1 << 20       # an aligned address that nothing reads
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    stub = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", stub, os.path.join(HERE, "hip_stub.c")], check=True)
+
+    def go(body):
+        r = subprocess.run([sys.executable, "-c", PRELUDE % {"root": ROOT, "stub": stub} + body],
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return go
+
+
+def test_lds_limits_do_not_depend_on_the_call(run):
+    """A kernel's limit of dynamic LDS belongs to the process: if every call set it to its
+    own network's need, a thread with a small network could lower it between another
+    thread's call and launch.  Every call sets the same value, which no launch exceeds."""
+    run("""
+for L, hidden in ((1023, 256), (21, 64), (501, 256)):
+    lay = labs.mlp_layout(L, hidden)
+    r = ctypes.byref(lay)
+    assert H.labs_mlp_train_step(r, P, P, P, P, P, 1, 1e-3, .9, .999, 1e-8, 100, P, P, P, P, P, 1 << 40, None) == 0
+    assert H.labs_mlp_grads(r, P, P, 100, P, P, P, P, P, P, 1 << 40, None) == 0
+    for n in (1, 5000, 20000):
+        assert H.labs_mlp_forward(r, P, P, n, P, P, P, 1 << 40, None) == 0
+limit = {}
+for a in attrs():
+    limit.setdefault(a.name, set()).add(a.value)
+assert len(limit) >= 4, limit       # two training kernels, the forward's row tiles
+assert all(len(v) == 1 for v in limit.values()), limit
+for l in launches():
+    if l.shmem > 64 * 1024:
+        assert l.shmem <= min(limit[l.name])
+""")
