@@ -239,7 +239,7 @@ labs_status labs_walk_step1_bloom(const labs_step1_cfg* cfg, const labs_bloom* b
  * Autotuner of the walker's persistent launches.  A shape class is (NW, R): NW =
  * ceil(k/32) words of even lags and R = ceil((k+1-p)/64) groups of free positions (at
  * least ceil(NW/2) - 1).  What is tuned is the resident waves per SIMD that persistent
- * launches request (1, 2, 3, 4 or 8; untuned 5); a table's RB (R or ceil(R/2)) is kept
+ * launches request (1, 2, 3, 4 or 8; untuned 8); a table's RB (R or ceil(R/2)) is kept
  * and reported, and every kernel scans all positions at once.  labs_autotune_step1
  * times every candidate on the largest
  * length of each class among Ls (host array of n_L odd lengths) with `walkers`

@@ -25,9 +25,14 @@ struct Tile {
     double ms;     // measured time of the winning trial (0 when untuned)
 };
 
-// Waves per SIMD a persistent launch asks for untuned: as many as the widest kernels
-// keep resident (workgroups beyond the residency find the queue empty and leave).
-constexpr int kDefaultWaves = 5;
+// Waves per SIMD a persistent launch asks for untuned: more than any kernel keeps resident
+// (workgroups beyond the residency find the queue empty and leave), and one of the
+// autotuner's candidates, so that tuning never leaves a class slower than it was.  Eight
+// against five, us a batch: 75 lengths of 301..449, 256 walkers 7,890 and 8,030; two of
+// 16,384 walkers at L = 101 2,760 and 3,000, of 20,000 at L = 301 1,410 and 1,520, of 8,192
+// at L = 501 1,200 and 1,190; lengths 531..639, 64 walkers 1,220 and 1,230.
+constexpr int kDefaultWaves = 8;
+constexpr int kWaveCandidates[] = {1, 2, 3, 4, kDefaultWaves};
 
 std::mutex g_mu;
 std::map<std::pair<int, int>, Tile> g_tiles;   // (NW, R) -> tile
@@ -477,7 +482,7 @@ labs_status autotune_step1(const int32_t* Ls, int n_L, int p, int walkers, int s
         hipEventCreate(&a);
         hipEventCreate(&b);
         labs_status s = LABS_OK;
-        for (int waves : {1, 2, 3, 4, 8}) {
+        for (int waves : kWaveCandidates) {
             Tile t{sh.R, waves, 0};
             s = batch_walk(&c, 1, &o, ws, bl.total, st, &t, false);   // warm-up
             if (s != LABS_OK) break;

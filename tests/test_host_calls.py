@@ -69,3 +69,20 @@ for l in launches():
     if l.shmem > 64 * 1024:
         assert l.shmem <= min(limit[l.name])
 """)
+
+
+@pytest.mark.parametrize("L", [101, 301, 501, 639])
+def test_autotuner_times_the_untuned_residency(run, L):
+    """The tuner replaces the residency that an untuned launch asks for, so it has to have
+    timed it: where that one is the fastest, tuning keeps it."""
+    run("""
+L, p, walkers = %d, 16, 20000
+untuned = labs.autotune_get(L, p)
+F = ctypes.CFUNCTYPE(ctypes.c_float, ctypes.c_uint32)
+elapsed = F(lambda grid: 1.0 + abs(int(grid) - 4 * 256 * untuned[1]))     # 256 CUs, 4 SIMDs each
+ctypes.c_void_p.in_dll(S, "elapsed_of_grid").value = ctypes.cast(elapsed, ctypes.c_void_p).value
+ctypes.c_char_p.in_dll(S, "timed_kernel").value = b"k_walk_persistent"
+assert H.labs_autotune_step1((ctypes.c_int32 * 1)(L), 1, p, walkers, 10, None) == 0
+assert sum(b"k_walk_persistent" in l.name for l in launches()) >= 10
+assert labs.autotune_get(L, p) == untuned
+""" % L)
