@@ -647,7 +647,7 @@ labs_status learned_walk(const labs_step1_cfg& c, const labs_proposer& pr, const
     w.log_mask = A.log_mask;
     w.log_label = A.log_label;
     const bool packed = mlp && mlp_packs(lay);
-    if (F > 1 && packed && (s = mlp_pack(lay, pr.params_bf16, B.fwd_ws, B.fwd_bytes, st))) return s;
+    if (F > 1 && c.steps > 1 && packed && (s = mlp_pack(lay, pr.params_bf16, B.fwd_ws, B.fwd_bytes, st))) return s;
     for (int t = 1; t <= c.steps;) {
         if ((t - 1) % F == 0) {
             w.t0 = t - 1;

@@ -22,6 +22,11 @@ labs_status check_layout(const labs_mlp_layout* y) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// What a network pass keeps in its workspace is read and written 16 bytes at a time.
+labs_status check_ws(const void* ws) {
+    return aligned16(ws) ? LABS_OK : invalid("workspace must be 16-byte aligned");
+}
+
 labs_status check_rows(int64_t n) {
     if (n < 0 || n > (int64_t)INT32_MAX / 2) return invalid("n must be in [0, 2^30)");
     return LABS_OK;
@@ -87,6 +92,8 @@ labs_status labs_learned_walk(const labs_step1_cfg* cfg, const labs_proposer* pr
         return invalid("log_every > 0 needs log_seqs, log_mask and log_label");
     const labs_step1_cfg c = with_default_steps(*cfg);
     if (!ws || ws_bytes < learned_walk_ws(c, *prop)) return invalid("workspace too small");
+    if (prop->mode == LABS_PROPOSE_MLP && prop->fallback_every > 1 && c.steps > 1)   // some step runs the network
+        if (labs_status s = check_ws(ws)) return s;
     return learned_walk(c, *prop, *out, ws, ws_bytes, S(stream));
 }
 
@@ -127,6 +134,7 @@ labs_status labs_mlp_forward(const labs_mlp_layout* lay, const float* params, co
     if (!params || !params_bf16 || !X || !logits || !ws) return invalid("pointers must not be NULL");
     if (!aligned16(params_bf16) || !aligned16(X)) return invalid("params_bf16 and X must be 16-byte aligned");
     if (ws_bytes < mlp_forward_ws(*lay, n)) return invalid("workspace too small");
+    if (labs_status s = check_ws(ws)) return s;
     return mlp_forward(*lay, params, params_bf16, n, X, logits, ws, ws_bytes, S(stream));
 }
 
@@ -149,6 +157,8 @@ labs_status labs_mlp_grads(const labs_mlp_layout* lay, const float* params, cons
     if (n > 0 && (!X || !mask || !labels)) return invalid("X, mask and labels must not be NULL");
     if (!aligned16(params_bf16) || (X && !aligned16(X))) return invalid("params_bf16 and X must be 16-byte aligned");
     if (ws_bytes < mlp_grads_ws(*lay, n)) return invalid("workspace too small");
+    if (n > 0)
+        if (labs_status s = check_ws(ws)) return s;
     return mlp_grads(*lay, params, params_bf16, n, X, mask, labels, grads, loss, ws, ws_bytes, S(stream));
 }
 
@@ -191,7 +201,7 @@ labs_status labs_mlp_train_step(const labs_mlp_layout* lay, float* params, uint1
     if (!aligned16(params_bf16)) return invalid("params_bf16 must be 16-byte aligned");
     const size_t xb = train_features_bytes(*lay, n);
     if (ws_bytes < xb + mlp_grads_ws(*lay, n)) return invalid("workspace too small");
-    if (!aligned16(ws)) return invalid("workspace must be 16-byte aligned");
+    if (labs_status s = check_ws(ws)) return s;
     if (mlp_packs(*lay) && n > 0) {
         const MlpAdam adam{m, v, t, lr, beta1, beta2, eps};
         return mlp_train(*lay, params, params_bf16, n, seqs, nullptr, mask, labels, grads, loss, &adam, ws, ws_bytes,

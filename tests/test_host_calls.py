@@ -86,3 +86,40 @@ assert H.labs_autotune_step1((ctypes.c_int32 * 1)(L), 1, p, walkers, 10, None) =
 assert sum(b"k_walk_persistent" in l.name for l in launches()) >= 10
 assert labs.autotune_get(L, p) == untuned
 """ % L)
+
+
+def test_network_workspaces_are_16_byte_aligned(run):
+    """The network's kernels read and write their workspace 16 bytes at a time: one that
+    is not aligned for that is refused before any launch, at every width.  Calls that run
+    no network take any."""
+    run("""
+for hidden in (64, 256, 320):
+    lay = labs.mlp_layout(101, hidden)
+    r = ctypes.byref(lay)
+    for off in (1, 4, 8):
+        W = P + off
+        assert H.labs_mlp_forward(r, P, P, 100, P, P, W, 1 << 40, None) == -1
+        assert b"16-byte" in H.labs_last_error()
+        assert H.labs_mlp_grads(r, P, P, 100, P, P, P, P, P, W, 1 << 40, None) == -1
+        assert H.labs_mlp_train_step(r, P, P, P, P, P, 1, 1e-3, .9, .999, 1e-8, 100, P, P, P, P, W, 1 << 40, None) == -1
+    assert not launches()
+
+def walk(mode, every, steps, ws, hidden):
+    cfg = labs.Step1Cfg(101, 8, steps, 10, 20, -1, 0, 100, 1, 0, 0)
+    pr = labs.Proposer(mode, 8, every, hidden, P, P, 0, 0, 0)
+    out = labs.LearnedOut()
+    out.flip_evals = P
+    return H.labs_learned_walk(ctypes.byref(cfg), ctypes.byref(pr), ctypes.byref(out), ws, 1 << 40, None)
+
+for hidden in (64, 320):
+    assert walk(labs.PROPOSE_MLP, 4, 10, P + 8, hidden) == -1 and b"16-byte" in H.labs_last_error()
+    assert not launches()
+    assert walk(labs.PROPOSE_MLP, 4, 10, P + 16, hidden) == 0
+    assert walk(labs.PROPOSE_MLP, 1, 10, P + 8, hidden) == 0
+    assert walk(labs.PROPOSE_MLP, 4, 1, P + 8, hidden) == 0
+    assert walk(labs.PROPOSE_RANDOM, 4, 10, P + 8, hidden) == 0
+    ctypes.c_int.in_dll(S, "stub_n_launches").value = 0
+lay = labs.mlp_layout(101, 64)
+assert H.labs_mlp_grads(ctypes.byref(lay), P, P, 0, None, None, None, P, P, P + 4, 1 << 40, None) == 0
+assert H.labs_mlp_forward(ctypes.byref(lay), P, P, 0, P, P, P + 4, 1 << 40, None) == 0
+""")
