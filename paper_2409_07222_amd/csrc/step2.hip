@@ -2106,7 +2106,23 @@ __global__ __launch_bounds__(kRotThreads) void k_rot_stage(Params P) {
             const uint32_t i0 = (uint32_t)(d >> 20) & (kRotBits - 1), i1 = (uint32_t)(d >> 40) & (kRotBits - 1);
             if (d > 1 && !((zbits[0][i0 >> 5] >> (i0 & 31)) & (zbits[1][i1 >> 5] >> (i1 & 31)) & 1u)) continue;
             const int at = atomicAdd(&s_near, 1);
-            if (at < kRotNear) near[at] = make_int2(q, (int)v);
+            if (at < kRotNear) {
+                near[at] = make_int2(q, (int)v);
+            } else {
+                // No room in the list (256 pairs; by chance alone one in 4,000 of n_piv 2 T_r
+                // at L = 500, one in 1,000 at L = 1,001): this thread compares the words,
+                // which mostly differ in the first.  Comparing every pivot again instead
+                // made large batches slow: 32,768 pivots at L = 500, T_r = 32, three rounds
+                // 2,737 ms, now 418; 8,192 at L = 1,001, four rounds 266, now 73.
+                const uint32_t* pv = P.H.seq + (size_t)P.piv[v] * W;
+                int n = 0;
+                for (int w = 0; w < W && n <= 1; ++w) {
+                    uint32_t x = rw[q][w] ^ pv[w];
+                    if (w == W - 1) x &= last_mask;
+                    n += __popc(x);
+                }
+                if (n <= 1) dupq[q] = 1;
+            }
         }
     }
     __syncthreads();
@@ -2143,19 +2159,6 @@ __global__ __launch_bounds__(kRotThreads) void k_rot_stage(Params P) {
             }
         }
     }
-    // more pivots near than the list holds: all of them, one by one
-    if (s_near > kRotNear)
-        for (long long v = t; v < np; v += kRotThreads)
-            for (int q = 0; q < R2; ++q) {
-                const uint32_t* pv = P.H.seq + (size_t)P.piv[v] * W;
-                int d = 0;
-                for (int w = 0; w < W && d <= 1; ++w) {
-                    uint32_t x = rw[q][w] ^ pv[w];
-                    if (w == W - 1) x &= last_mask;
-                    d += __popc(x);
-                }
-                if (d <= 1) dupq[q] = 1;
-            }
     __syncthreads();
     if (t < R2) {
         const int q = t;

@@ -217,3 +217,24 @@ def test_step2_wide_energy_range(lb, orc, L, B, Q, X):
         assert (max(E) - min(E)) // 4 >= 1 << 14
     _run_both(lb, orc, L, cands, B, Q, X, 1 << 40)
     _run_both(lb, orc, L, cands, B, Q, X, 1 << 40, T_r=2)
+
+
+@pytest.mark.parametrize("L,T_r,rolls,flips", [(96, 16, 40, 12), (33, 16, 33, 33)])
+def test_step2_rotations_with_more_near_pivots_than_the_list(lb, orc, L, T_r, rolls, flips):
+    """One round whose pivots are the rotations of one sequence and their single flips: a
+    pivot's 32 rotations have more than 256 pivots within one flip, so a part of the pairs
+    is compared beside the list."""
+    c = li.random_pm1(L + 5, 1, L)[0]
+    cands = []
+    for r in range(rolls):
+        x = np.roll(c, r)
+        cands.append(x)
+        for f in range(0, L, L // flips):
+            y = x.copy()
+            y[f] = -y[f]
+            cands.append(y)
+    cands = np.unique(np.stack(cands), axis=0)
+    mid = rolls // 2
+    rot = np.stack([np.roll(c, mid + r) for r in range(-T_r, T_r + 1) if r])     # of the pivot np.roll(c, mid)
+    assert ((cands[:, None] != rot[None]).sum(2) <= 1).sum() > 256 and len(cands) <= 1200
+    _run_both(lb, orc, L, cands, 1200, 4000, len(cands), 1 << 40, T_r)
