@@ -357,6 +357,16 @@ __global__ __launch_bounds__(256) void k_features(int L, int W, int64_t n, const
     const uint32_t* u = sw[wv];
     uint16_t* x = X + r * ld_in;
     const int k = (L - 1) / 2;
+    // L <= 43: one element a lane and one store (2^20 rows at L = 21 131 us; the three
+    // stores below 155, a generic shift and an exact division 143)
+    if (ld_in == 64) {
+        const int m = lane - L + 1;
+        uint16_t v = 0;
+        if (lane < L) v = packed_bit(u, lane + 1) ? 0x3F80 : 0xBF80;
+        else if (m <= k) v = corr_feature(packed_corr(u, L, 2 * m), corr_scale(L, m));
+        x[lane] = v;
+        return;
+    }
     for (int i = lane; i < k; i += 64) {          // elements 2i, 2i + 1; the last one below
         const uint32_t b = ~u[i >> 4] << (2 * (i & 15));
         ((uint32_t*)x)[i] = 0x3F803F80u | ((b >> 16) & 0x8000u) | ((b & 0x40000000u) << 1);

@@ -66,6 +66,20 @@ def test_features_bit_exact(lb, orc, L):
     assert np.all(got[:, lay.d_in:] == 0)
 
 
+@pytest.mark.parametrize("L", [5, 7, 31, 33, 41, 43, 45, 47])
+@pytest.mark.parametrize("n", [1, 5, 64])
+def test_features_of_short_rows(lb, orc, L, n):
+    """Rows of 64 elements (L <= 43) take one store, longer ones several: bit for bit."""
+    S = li.random_pm1(500 + L, n, L)
+    X = lb.mlp_features(L, _dev_i32(li.pack(S)))
+    lay = lb.mlp_layout(L, 64)
+    assert lay.ld_in == (64 if L <= 43 else 128)
+    want = omlp.bf16_round(omlp.features(S, _c_even(orc, S)).astype(np.float32))
+    got = X.float().cpu().numpy()
+    assert np.array_equal(got[:, :lay.d_in].view(np.uint32), want.view(np.uint32))
+    assert np.all(got[:, lay.d_in:] == 0)
+
+
 @pytest.mark.parametrize("L,hidden,n", [(37, 64, 1), (101, 128, 300), (501, 256, 257), (501, 256, 1000), (101, 64, 700)])
 def test_forward_logits(lb, orc, L, hidden, n):
     lay, P, blob, pb = _params(lb, L, hidden, 55)
