@@ -341,6 +341,11 @@ labs_status gemm(bool a_k, bool b_k, int M, int N, int K, const uint16_t* A, int
 }
 
 // ------------------------------------------------------------------ features
+// X need only be aligned for its 2-byte elements.
+struct __attribute__((packed, aligned(2))) TwoElements {
+    uint32_t v;
+};
+
 // x = (s_1..s_L as +1/-1, C_{2m}/(L-2m) for m = 1..k, zeros to ld_in), bf16.
 // One wave per sequence; a lane writes two elements of the sequence part at a time and
 // takes every 64th lag.  Bound by the popcounts of the lags and the stores: with a generic
@@ -369,7 +374,7 @@ __global__ __launch_bounds__(256) void k_features(int L, int W, int64_t n, const
     }
     for (int i = lane; i < k; i += 64) {          // elements 2i, 2i + 1; the last one below
         const uint32_t b = ~u[i >> 4] << (2 * (i & 15));
-        ((uint32_t*)x)[i] = 0x3F803F80u | ((b >> 16) & 0x8000u) | ((b & 0x40000000u) << 1);
+        ((TwoElements*)x)[i].v = 0x3F803F80u | ((b >> 16) & 0x8000u) | ((b & 0x40000000u) << 1);
     }
     if (lane == 0) x[L - 1] = packed_bit(u, L) ? 0x3F80 : 0xBF80;
     for (int i = lane; i < ld_in - L; i += 64)

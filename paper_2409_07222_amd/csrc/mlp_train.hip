@@ -419,6 +419,11 @@ struct AdamArgs {
     float b1, omb1, b2, omb2, bc1, bc2, lr, eps;
 };
 
+// The caller's gradients need only be aligned for their elements.
+struct __attribute__((packed, aligned(4))) FourGrads {
+    float v[4];
+};
+
 // Gradient of four consecutive parameters (a region's start and row lengths are multiples
 // of 64), zero in the pads; with ADAM also the update.
 template <bool ADAM>
@@ -465,7 +470,7 @@ __global__ __launch_bounds__(256) void k_grads_final(TrainArgs T, float* __restr
 #pragma unroll
     for (int r = 0; r < 4; ++r)
         if (r >= live) g[r] = 0.f;
-    *(float4*)(G + i0) = make_float4(g[0], g[1], g[2], g[3]);
+    *(FourGrads*)(G + i0) = FourGrads{{g[0], g[1], g[2], g[3]}};
     if constexpr (ADAM) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)

@@ -219,6 +219,34 @@ def test_training_pass_edges(lb, orc, L, hidden, n):
         assert torch.equal(x[0], x[1])
 
 
+@pytest.mark.parametrize("L,hidden,n", [(37, 64, 40), (101, 128, 65)])
+def test_buffers_aligned_for_their_elements_only(lb, L, hidden, n):
+    """Feature rows may start at any bf16 and gradients at any float: the results there
+    are those at aligned addresses."""
+    import ctypes
+    import torch
+    lay, _, blob, pb = _params(lb, L, hidden, 62)
+    S = li.random_skew(23 * L, n, L, 0)
+    seqs = _dev_i32(li.pack(S))
+    X = lb.mlp_features(L, seqs)
+    _, labels, words = _mask_labels(L + 2, n, lay.d_out)
+    mask, lab = _dev_i32(words), torch.from_numpy(labels).cuda()
+    G, loss = lb.mlp_grads(lay, blob, pb, X, mask, lab)
+    H, r = lb.lib(), ctypes.byref(lay)
+    ws = lb._ws("labs_mlp_grads_workspace", lay, n, X.device, None)
+    for off in (1, 2, 3):
+        x = torch.zeros(n * lay.ld_in + 8, dtype=torch.bfloat16, device="cuda")
+        g = torch.zeros(lay.n_params + 8, dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        lb._check(H.labs_mlp_features(L, n, lb._ptr(seqs), x[off:].data_ptr(), lb._stream(x.device)))
+        lb._check(H.labs_mlp_grads(r, lb._ptr(blob), lb._ptr(pb), n, lb._ptr(X), lb._ptr(mask), lb._ptr(lab),
+                                   g[off:].data_ptr(), lb._ptr(loss), lb._ptr(ws), ws.numel(), lb._stream(x.device)))
+        torch.cuda.synchronize()
+        assert torch.equal(x[off:off + X.numel()], X.flatten()) and torch.equal(g[off:off + G.numel()], G)
+        assert not x[:off].any() and not x[off + X.numel():].any()
+        assert not g[:off].any() and not g[off + G.numel():].any()
+
+
 def omlp_keys():
     return ("W1", "b1", "W2", "b2", "W3", "b3")
 
