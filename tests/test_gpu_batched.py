@@ -103,3 +103,27 @@ def test_autotune_and_half_tile_parity(lb, orc, tmp_path):
         r = lb.walk_step1(L, p, steps, lo, hi, 17, n, want_traj=True)
         o = orc.walk(L, p, steps, lo, hi, 17, range(n))
         assert np.array_equal(r.traj_E.cpu().numpy(), o["traj"]), L
+
+
+@pytest.mark.parametrize("waves", [1, 3, 8])
+def test_batched_at_forced_residencies(lb, orc, tmp_path, waves):
+    """What a table file changes is the residency that the batched launches ask for: walks
+    at the least, a middle and the largest one, against the oracle's."""
+    import torch
+    cfgs = _cfgs([45, 131, 331, 513, 639], 3, 60, seed=21)
+    path = str(tmp_path / "waves.json")
+    with open(path, "w") as f:
+        rows = []
+        for c in cfgs:
+            k = (c["L"] - 1) // 2
+            NW = (k + 31) // 32
+            R = max((k + 1 - c["p"] + 63) // 64, (NW + 1) // 2 - 1, 1)
+            rows.append({"NW": NW, "R": R, "RB": R, "waves_per_simd": waves, "trial_ms": 0})
+        f.write(json.dumps({"walker_tiles": rows}).replace('{"NW"', '\n{"NW"'))
+    lb.autotune_load(path)
+    assert all(lb.autotune_get(c["L"], c["p"])[1] == waves for c in cfgs)
+    res, _ = lb.walk_step1_batch(cfgs, want_traj=True)
+    torch.cuda.synchronize()
+    for c, r in zip(cfgs, res):
+        o = orc.walk(c["L"], c["p"], c["steps"], c["tenure_lo"], c["tenure_hi"], c["seed"], range(3))
+        assert np.array_equal(r.traj_E.cpu().numpy(), o["traj"]), c["L"]

@@ -219,6 +219,37 @@ def test_training_pass_edges(lb, orc, L, hidden, n):
         assert torch.equal(x[0], x[1])
 
 
+@pytest.mark.parametrize("L,hidden,n", [(37, 64, 1), (53, 192, 130), (101, 256, 511), (501, 256, 1000),
+                                        (501, 256, 2000), (1023, 256, 600)])
+def test_gradients_equal_the_separate_products(lb, L, hidden, n):
+    """The four-launch gradients against the separate products, which a network of 320
+    units takes: the same one widened by units of zero weights, which add exact zeros.
+    At these row counts both split the batch alike (by 256 rows at least), so every sum
+    has the same order and loss and gradients are equal bit for bit."""
+    import torch
+    lay, P, blob, pb = _params(lb, L, hidden, 63)
+    wide = lb.mlp_layout(L, 320)
+    Q = {key: np.zeros(s, np.float32) for key, s in
+         (("W1", (320, lay.d_in)), ("b1", 320), ("W2", (320, 320)), ("b2", 320),
+          ("W3", (lay.d_out, 320)), ("b3", lay.d_out))}
+    for key in Q:
+        Q[key][tuple(slice(0, d) for d in P[key].shape)] = P[key]
+    wblob = torch.from_numpy(lb.mlp_blob_from_dict(wide, Q)).cuda()
+    wpb = torch.empty(wide.n_params, dtype=torch.bfloat16, device="cuda")
+    lb.mlp_cast(wide, wblob, wpb)
+    X = lb.mlp_features(L, _dev_i32(li.pack(li.random_skew(29 * L, n, L, 0))))
+    _, labels, words = _mask_labels(L + 3, n, lay.d_out)
+    mask, lab = _dev_i32(words), torch.from_numpy(labels).cuda()
+    g, loss = lb.mlp_grads(lay, blob, pb, X, mask, lab)
+    wg, wloss = lb.mlp_grads(wide, wblob, wpb, X, mask, lab)
+    g, wg = lb.mlp_dict_from_blob(lay, g.cpu().numpy()), lb.mlp_dict_from_blob(wide, wg.cpu().numpy())
+    assert float(loss.item()) == float(wloss.item())
+    for key in omlp_keys():
+        inner = wg[key][tuple(slice(0, d) for d in g[key].shape)]
+        assert np.array_equal(g[key], inner), (key, int((g[key] != inner).sum()))
+        assert np.count_nonzero(wg[key]) == np.count_nonzero(inner), key
+
+
 @pytest.mark.parametrize("L,hidden,n", [(37, 64, 40), (101, 128, 65)])
 def test_buffers_aligned_for_their_elements_only(lb, L, hidden, n):
     """Feature rows may start at any bf16 and gradients at any float: the results there

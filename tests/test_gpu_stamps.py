@@ -145,3 +145,25 @@ def test_learned_walk_stamps(lb, mode):
     best = min(lowest, int(r2["best_E"].min().item()))
     for l, e in enumerate(levels):
         assert (ticks[l] != NEVER) == (best <= e)
+
+
+@pytest.mark.parametrize("L,p,n", [(101, 8, 4097), (201, 16, 8193)])
+def test_several_walkers_a_wave_stamp_levels(lb, L, p, n):
+    """Walks of four or two walkers a wave stamp their levels by code of their own: which
+    levels are hit follows from the same walkers' best energies one to a wave."""
+    import torch
+    steps, lo, hi = 300, L // 10, L // 5
+    one = lb.learned_walk(L, p, steps, lo, hi, 5, n, mode=lb.PROPOSE_RANDOM, top_m=1, fallback_every=1)
+    best = one["best_E"].cpu().numpy()
+    least = int(best.min())
+    levels = [least - 4, least, int(np.median(best)), 10 ** 7]
+    st = lb.Stamps(levels)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    r = lb.walk_step1(L, p, steps, lo, hi, 5, n, stamps=st)
+    torch.cuda.synchronize()
+    el = time.perf_counter() - t0
+    assert np.array_equal(r.best_E.cpu().numpy(), best)
+    ticks = _check_times(lb, st, el)
+    assert [t != NEVER for t in ticks] == [False, True, True, True]
+    assert ticks[3] < ticks[1]           # some walker starts below the last level

@@ -367,6 +367,37 @@ def test_several_walkers_a_wave_fill_the_same_pool(lb, L, p):
         assert np.array_equal(getattr(one, key)[:c].cpu().numpy(), getattr(four, key)[:c].cpu().numpy()), key
 
 
+@pytest.mark.parametrize("L,p,n", [(37, 2, 4098), (101, 8, 4097), (107, 8, 8193), (201, 12, 8193)])
+def test_several_walkers_a_wave_go_on_in_the_next_launch(lb, L, p, n):
+    """More steps than one launch holds: walkers that share a wave take up tabu deadlines,
+    correlations and bests where the launch before left them, as walkers alone do."""
+    steps, lo, hi = 4200, L // 10, L // 5
+    a = lb.walk_step1(L, p, steps, lo, hi, 29, n)
+    b = lb.learned_walk(L, p, steps, lo, hi, 29, n, mode=lb.PROPOSE_RANDOM, top_m=1, fallback_every=1)
+    for key in ("final_seqs", "final_E", "best_seqs", "best_E", "best_step"):
+        assert np.array_equal(getattr(a, key).cpu().numpy(), b[key].cpu().numpy()), key
+    if L > 100:                          # shorter walks have their optimum long before
+        assert int((a.best_step > 4096).sum().item()) > 0
+
+
+@pytest.mark.parametrize("L,p", [(101, 8), (201, 12)])
+def test_several_walkers_a_wave_fill_the_same_pool_over_segments(lb, L, p):
+    """With a pool a launch holds 256 steps at first: 900 steps of 8,192 walkers in shared
+    waves against four calls of 2,048 walkers a wave each."""
+    lo, hi, steps, e_max = L // 10, L // 5, 900, L * L // 10
+    one, four = lb.PoolBuffers.empty(L, 1 << 18), lb.PoolBuffers.empty(L, 1 << 18)
+    lb.walk_step1(L, p, steps, lo, hi, 3, 8192, e_max=e_max, pool=one, pool_walker_best=True)
+    for q in range(4):
+        lb.walk_step1(L, p, steps, lo, hi, 3, 2048, walker_begin=2048 * q, e_max=e_max, pool=four,
+                      pool_walker_best=True)
+    c = int(one.count.item())
+    assert c > 8000 and c == int(four.count.item())
+    assert int(one.dropped.item()) == int(four.dropped.item()) == 0
+    assert int(one.step[:c].max().item()) > 256
+    for key in ("E", "seqs", "walker", "step"):
+        assert np.array_equal(getattr(one, key)[:c].cpu().numpy(), getattr(four, key)[:c].cpu().numpy()), key
+
+
 # ------------------------------------------------------------------ edges of the walk kernel
 # Lengths on both sides of every size the matrix-core scan is instantiated at: the class
 # rows grow by 32 indices where k + 12 passes a multiple of 32 (L = 105/107, 169/171, ...,
