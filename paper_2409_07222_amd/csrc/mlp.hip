@@ -685,14 +685,16 @@ static int64_t packed_total(const labs_mlp_layout& y) {
 }
 
 // Row tiles a workgroup.  While one workgroup a CU holds every row, the fewest tiles that
-// do (L = 501, hidden 256: 4,096 rows 17.5 us at one, 19.4 at two, 25.2 at four; 8,192
-// rows 25.8, 21.3, 26.7).  Beyond, four tiles read each weight least often but leave one
-// workgroup a CU, so a last round that is at most half full costs more than it saves:
-// 16,384 rows 33.0 us at two and 29.7 at four, 20,480 rows 44.9 and 49.7 (with the GELU of that time).
+// do: with the weights read from the L2 by every workgroup, fewer rows a workgroup finish
+// sooner.  Beyond, workgroups follow one another on a CU, and two tiles, of which two or
+// more workgroups share a CU, hide each other's phases where four leave one alone.
+// L = 501, hidden 256, us at one, two and four tiles: 4,096 rows 17.4, 19.3, 24.5; 8,192
+// 24.1, 20.3, 25.4; 12,288 31.6, 27.3, 25.7; 16,384 40.2, 29.6, 28.0; 20,480 47.8, 40.7,
+// 46.2; 32,768 70.4, 51.7, 53.5; 65,536 131, 91.5, 99.3.  The same order at L = 101,
+// hidden 128 (65,536 rows 43.3, 32.8, 36.2) and L = 21, hidden 64 (29.6, 25.7, 28.9).
 static int forward_tiles(const labs_mlp_layout& y, int64_t n) {
     constexpr int kCUs = 256;
-    const int64_t last = (n + 63) / 64 % kCUs;
-    int mr = n <= 16 * kCUs ? 1 : n <= 32 * kCUs || (last > 0 && last <= kCUs / 2) ? 2 : 4;
+    int mr = n <= 16 * kCUs ? 1 : n > 32 * kCUs && n <= 64 * kCUs ? 4 : 2;
     while (mr > 1 && forward_lds(mr, y.ld_in, y.hidden) > kLdsBytes) mr /= 2;
     return mr;
 }

@@ -91,6 +91,19 @@ def test_forward_logits(lb, orc, L, hidden, n):
     assert err.max() <= 1e-2, err.max()
 
 
+@pytest.mark.parametrize("L,hidden", [(21, 64), (101, 256), (1023, 256)])
+@pytest.mark.parametrize("n", [8193, 16384, 16385, 40001])
+def test_forward_of_many_rows_equals_that_of_few(lb, L, hidden, n):
+    """32 rows a workgroup, 64 up to 16,384 rows, then 32 again: each row's logits are
+    those of a pass over at most 4,096 rows (16 a workgroup), bit for bit."""
+    import torch
+    lay, _, blob, pb = _params(lb, L, hidden, 64)
+    X = lb.mlp_features(L, _dev_i32(li.pack(li.random_pm1(41 * L, n, L))))
+    z = lb.mlp_forward(lay, blob, pb, X)[:, :lay.d_out]
+    few = torch.cat([lb.mlp_forward(lay, blob, pb, x)[:, :lay.d_out] for x in X.split(4096)])
+    assert torch.equal(z.contiguous().view(torch.int32), few.view(torch.int32))
+
+
 def test_forward_logits_128_tiles(lb, orc):
     """33,000 rows at L = 501, hidden 256: the grid of 128 x 128 tiles holds 516
     workgroups, so the forward runs the 128-tile kernel; its last row tile is
