@@ -15,12 +15,8 @@ namespace labsdev {
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
 constexpr int kWaves = 4;    // sequences a workgroup
 constexpr int kMaxW = 32;
-
-__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Popcounts of the lags are the bound.  4,096 sequences at L = 501 with C: byte loops over
 // LDS 222 us, now 9.6.

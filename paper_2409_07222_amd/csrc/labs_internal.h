@@ -49,8 +49,11 @@ extern "C" __device__ int __ockl_wfred_min_i32(int);
 extern "C" __device__ unsigned int __ockl_wfred_or_u32(unsigned int);
 extern "C" __device__ int __ockl_wfred_add_i32(int);
 extern "C" __device__ unsigned int __ockl_wfred_max_u32(unsigned int);
-extern "C" __device__ int __ockl_wfred_max_i32(int);
-extern "C" __device__ int __ockl_wfscan_add_i32(int, bool);
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// Orders one wavefront's LDS accesses for the compiler (the hardware runs them in order).
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // popcount(x) + acc in one instruction: bit-plane sums chain through the
 // accumulator operand of v_bcnt_u32_b32 (written out, because the compiler splits
@@ -278,10 +281,10 @@ int walk_group(int L, int p, int64_t n);
 labs_status launch_walk_group(const WalkArgs& A, int G, hipStream_t st);
 labs_status launch_offer_best(const WalkArgs& A, hipStream_t st);
 labs_status launch_walk_outputs(const WalkArgs& A, const labs_step1_out& o, hipStream_t st);
-// Sorts records [0, n) of `rb` by key words 0..nkeys-1 (word 0 most significant),
+// Sorts records [0, n) of `rb` by their key words (word 0 most significant),
 // leaving the permutation in *perm_out (device array of n uint32, inside ws); `counts`
 // is scratch of n uint32.
-labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, uint32_t* counts, void* ws,
+labs_status radix_sort_records(const RecBuf& rb, int64_t n, uint32_t* counts, void* ws,
                                size_t ws_bytes, uint32_t** perm_out, hipStream_t st);
 
 // Learned proposal network (mlp.hip).

@@ -56,8 +56,6 @@ __device__ __forceinline__ uint32_t score_bits(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
 // A walker is a row of 16 lanes; lane patterns that exchange its halves, quarters, pairs.
 constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E, kSwap4 = 0x141, kSwap8 = 0x140;
 template <int CTRL>

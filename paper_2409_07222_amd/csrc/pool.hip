@@ -412,9 +412,9 @@ size_t sort_workspace_bytes(int64_t nmax, int32_t KW) {
     return b + 1024;
 }
 
-labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, uint32_t* counts, void* ws,
+labs_status radix_sort_records(const RecBuf& rb, int64_t n, uint32_t* counts, void* ws,
                                size_t ws_bytes, uint32_t** perm_out, hipStream_t st) {
-    if (rb.KW < 1 || rb.KW > kMaxKeyWords || nkeys > rb.KW) return invalid("record key words out of range");
+    if (rb.KW < 1 || rb.KW > kMaxKeyWords) return invalid("record key words out of range");
     Carve cv(ws, ws_bytes);
     const int64_t nblk = (n + kTile - 1) / kTile;
     uint32_t* p0 = cv.take<uint32_t>((size_t)n);
@@ -455,15 +455,16 @@ labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, uint3
     };
     // Leading words first where at least kLeadDigits digits behind them vary: a digit costs
     // three launches (8 to 12 us), the marks, the fix and its answer's way to the host about
-    // as much as four (a compaction's sort at L = 501: 69 digits 830 us, 10 and the fix 160).  A run that is too long to be put in order in place means all digits.
+    // as much as four (a compaction's sort at L = 501: 69 digits 830 us, 10 and the fix 160).
+    // A run that is too long to be put in order in place means all digits.
     constexpr int kLeadDigits = 8;
     const int W = rb.KW - 3;
     int behind = 0;
     for (int q = kLeadWords; q <= W; ++q)
         for (int byte = 0; byte < 4; ++byte) behind += ((hv[q] >> (8 * byte)) & 255u) != 0;
     labs_status s;
-    if (nkeys == rb.KW && behind >= kLeadDigits) {
-        for (int q = nkeys - 1; q > W; --q)
+    if (behind >= kLeadDigits) {
+        for (int q = rb.KW - 1; q > W; --q)
             if ((s = passes(q))) return s;
         for (int q = kLeadWords - 1; q >= 0; --q)
             if ((s = passes(q))) return s;
@@ -483,7 +484,7 @@ labs_status radix_sort_records(const RecBuf& rb, int64_t n, int32_t nkeys, uint3
         out = p1;
         hipLaunchKernelGGL(k_iota, dim3(blocks_for(n, 256)), dim3(256), 0, st, p0, n);
     }
-    for (int q = nkeys - 1; q >= 0; --q)
+    for (int q = rb.KW - 1; q >= 0; --q)
         if ((s = passes(q))) return s;
     *perm_out = in;
     return LABS_OK;
@@ -540,7 +541,7 @@ labs_status compact_records(const RecBuf& rb, int32_t W, int64_t n, int64_t cap,
     LABS_HIP(hipMemsetAsync(total, 0, sizeof(uint32_t) * 2, st));
     if (n > 0) {
         uint32_t* perm = nullptr;
-        labs_status s = radix_sort_records(rb, n, rb.KW, flag, sort_ws, sort_bytes, &perm, st);
+        labs_status s = radix_sort_records(rb, n, flag, sort_ws, sort_bytes, &perm, st);
         if (s != LABS_OK) return s;
         hipLaunchKernelGGL(k_unique_flags, dim3(blocks_for(n, 256)), dim3(256), 0, st, rb.rec, rb.stride,
                            W, perm, n, flag);

@@ -3,7 +3,8 @@
 //
 // One wavefront runs one walker.  Notation: L = 2k+1, even lags d = 2m,
 // m = 1..K with K = k (odd-lag C vanish for skew sequences, Sec. 1).  Free
-// positions a = p+1..k+1 (Eq. (3)); lane l owns a = p+1+l+64r, r = 0..R-1.
+// positions a = p+1..k+1 (Eq. (3)); a lane owns four consecutive ones of one class (below)
+// in each tile of 256.
 //
 // Energy change of the skew flip of a (partner b = L+1-a, partner lag
 // mp = (b-a)/2 = k+1-a).  Flipping a and b changes C_{2m} by -4 s_a u_m with
@@ -32,23 +33,16 @@
 // of f and 2 n_a - f, so it is kept per slot (v_dot4 on the bytes around the flip).
 // At the centre the two halves of H are equal: dE = -4 s_a H + 16 Mb.
 //
-// What bounds it: instruction issue, about 100 vector and 98 scalar instructions per
-// walker-step at L = 501 on each SIMD, and close behind it the LDS (132 cycles a
-// walker-step per CU, most of them the operands).  The popcount form this replaces
-// needed 915 vector instructions: 16,384 walkers at L = 501, p = 16, 26.7 -> 4.4 us a
-// step (1.44 -> 8.7e11 flip-evaluations/s); L = 301: 14.6 -> 3.8, L = 101: 4.2 -> 3.3,
-// L = 639: 42.5 -> 8.0 us.
+// What bounds it: instruction issue and the LDS together.  At L = 501 a walker-step takes
+// 103 vector and 96 scalar instructions on its SIMD and 117 LDS cycles on its CU, most of
+// them the operands: 0.68 of the VALU and 0.72 of the LDS peak.  The popcount form this
+// replaces needed 915 vector instructions: 16,384 walkers at L = 501, p = 16, 26.7 -> 4.1 us
+// a step (1.44 -> 9.5e11 flip-evaluations/s); L = 301: 14.6 -> 3.56, L = 639: 42.5 -> 8.0 us.
 #include "walk_impl.h"
 
 #include <climits>
 
 namespace labsdev {
-
-
-
-namespace {
-
-}  // namespace
 
 using namespace walkimpl;
 

@@ -8,19 +8,15 @@
 namespace labsdev {
 namespace walkimpl {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef short v2s __attribute__((ext_vector_type(2)));
 
-// a * b + c in one instruction, |a|, |b| < 2^23 (the intrinsic, not inline
+// a * b, |a|, |b| < 2^23, one instruction with a sum behind it (the intrinsic, not inline
 // assembly: the compiler has to see the hazards behind dot and matrix products).
 extern "C" __device__ int labs_mul_i24(int a, int b) __asm("llvm.amdgcn.mul.i24.i32");
 extern "C" __device__ int labs_mul_u24(int a, int b) __asm("llvm.amdgcn.mul.u24.i32");
-__device__ __forceinline__ int mad24(int a, int b, int c) { return labs_mul_i24(a, b) + c; }
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-// Orders one wavefront's LDS accesses for the compiler (the hardware runs them in order).
-__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // X holds, for class cl and shift i = 0..7, row cl*8 + i: byte kap is x_cl[i + kap - kz]
 // (0 outside the sequence), so any dword or 8-byte run of a class is one aligned
