@@ -349,8 +349,8 @@ struct __attribute__((packed, aligned(2))) TwoElements {
 // x = (s_1..s_L as +1/-1, C_{2m}/(L-2m) for m = 1..k, zeros to ld_in), bf16.
 // One wave per sequence; a lane writes two elements of the sequence part at a time and
 // takes every 64th lag.  Bound by the popcounts of the lags and the stores: with a generic
-// shift of two words and an exact division a term, 20,480 sequences at L = 501 took 40 us,
-// now 20.
+// shift of two words and an exact division a term, 20,480 sequences at L = 501 took 41 us,
+// now 23.
 __global__ __launch_bounds__(256) void k_features(int L, int W, int64_t n, const uint32_t* __restrict__ seqs,
                                                   uint16_t* __restrict__ X, int ld_in) {
     __shared__ uint32_t sw[4][36];
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(256) void k_pack_weights(labs_mlp_layout y, const u
 
 // The three layers of 16 MR rows by one workgroup: the feature rows and the hidden
 // activations stay in LDS, the packed weights are read from the L2 (655 KB a workgroup
-// at L = 501, hidden 256).  All workgroups run in step, so the phases add up: of 28.5 us
+// at L = 501, hidden 256).  All workgroups run in step, so the phases add up: of 28 us
 // for 16,384 rows the packing takes 4, the rows' load 5, GELU 4.6, the logits' stores 5.2;
 // with the weights, the rows or the products taken out the rest barely moves (2, 0, 1).
 // As three launches of tiled products the activations went through memory and the narrow

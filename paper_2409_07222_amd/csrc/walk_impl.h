@@ -628,7 +628,9 @@ __global__ __launch_bounds__(64, (WavesPerSimd<KH, NT>::value)) void k_walk(Walk
 // how many walkers reside; without the tabu deadlines a walker takes 1 KB less.  Registers
 // for five waves where the plain walk has six: 16,384 walkers at L = 451, us a step at 2^12,
 // 2^13, 2^15, 2^16 bits: 5.28, 5.13, 5.93, 7.35 (six 4.99, 5.28, 6.08, 7.47; with the
-// deadlines in LDS 5.44, 5.72, 6.53, 7.95).
+// deadlines in LDS 5.44, 5.72, 6.53, 7.95).  At 2^15 bits a walker-step takes 123 vector and
+// 126 scalar instructions and 112 LDS cycles, 0.55 of the VALU's and 0.50 of the LDS's time:
+// neither is full, the probes' chain and too few waves to cover it are the bound.
 template <int KH, int NT, int NQ>
 __global__ __launch_bounds__(64, (WavesPerSimd<KH, NT>::value > 5 ? 5 : WavesPerSimd<KH, NT>::value)) void k_walk_bloom(WalkArgs A) {
     __shared__ Lds<KH, NT, NQ, true> S;
