@@ -104,6 +104,21 @@ def test_forward_of_many_rows_equals_that_of_few(lb, L, hidden, n):
     assert torch.equal(z.contiguous().view(torch.int32), few.view(torch.int32))
 
 
+@pytest.mark.parametrize("L,hidden,n", [(37, 320, 22_100), (101, 512, 16_500)])
+def test_wide_forward_of_many_rows_equals_that_of_few(lb, L, hidden, n):
+    """Networks of more than 256 units run as separate products: at these row counts the
+    grid of 128 x 128 tiles holds 512 workgroups and the hidden layers take it; a pass over
+    at most 4,096 rows takes 64 x 64 tiles.  Both sum over K in the same order, so the
+    logits are equal bit for bit."""
+    import torch
+    lay, _, blob, pb = _params(lb, L, hidden, 65)
+    assert -(-n // 128) * -(-hidden // 128) >= 512
+    X = lb.mlp_features(L, _dev_i32(li.pack(li.random_pm1(43 * L, n, L))))
+    z = lb.mlp_forward(lay, blob, pb, X)[:, :lay.d_out]
+    few = torch.cat([lb.mlp_forward(lay, blob, pb, x)[:, :lay.d_out] for x in X.split(4096)])
+    assert torch.equal(z.contiguous().view(torch.int32), few.view(torch.int32))
+
+
 def test_forward_logits_128_tiles(lb, orc):
     """33,000 rows at L = 501, hidden 256: the grid of 128 x 128 tiles holds 516
     workgroups, so the forward runs the 128-tile kernel; its last row tile is
